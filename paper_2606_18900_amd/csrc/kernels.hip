@@ -1372,6 +1372,9 @@ int lz_launch_setup(lz_handle* h, hipStream_t s) {
   hipLaunchKernelGGL(k_fill_u32, dim3(grid), dim3(256), 0, s, h->ws.flags, nb, 0u);
   hipLaunchKernelGGL(k_fill_u32, dim3(grid), dim3(256), 0, s, h->ws.mark, nb, 0u);
   hipLaunchKernelGGL(k_fill_u64, dim3(grid), dim3(256), 0, s, h->ws.addr, nb, 0ull);
+  // k_closure takes a list entry as pushed once its upper half is the call's
+  // epoch (1, 2, ...): what the caller's memory held before must not look so
+  hipLaunchKernelGGL(k_fill_u64, dim3(grid), dim3(256), 0, s, h->ws.list, nb, 0ull);
   hipLaunchKernelGGL(k_fill_u32, dim3(1), dim3(64), 0, s, h->ws.ctl, (uint64_t)kCtlWords, 0u);
   return launch_ok("lz_open setup kernels");
 }
