@@ -132,6 +132,11 @@ __device__ __forceinline__ uint64_t ld64(const uint8_t* p) {
   return (uint64_t)ld32(p) | ((uint64_t)ld32(p + 4) << 32);
 }
 
+// 16 bytes from any address (one load: the device takes unaligned ones)
+typedef uint32_t u32x4 __attribute__((vector_size(16)));
+struct __attribute__((packed)) Any128 { u32x4 v; };
+__device__ __forceinline__ u32x4 ld128(const uint8_t* p) { return reinterpret_cast<const Any128*>(p)->v; }
+
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 // 16 bytes per lane straight from global memory into LDS, without registers
 // (global_load_lds_dwordx4): lane k's bytes land at dst + 16 k, dst being the
@@ -1978,25 +1983,71 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
   }
 }
 
-// One workgroup per (request, covering block) pair: copy the requested part
-// of a block that was decoded into a scratch slot.
-__global__ void k_req_gather(ReqArgs R) {
+// The same as find_req with every lane of a wave probing: 64 probes a step,
+// so two dependent loads for 4096 requests instead of twelve.
+__device__ __forceinline__ uint32_t find_req_wave(const uint64_t* v, uint32_t n, uint64_t g) {
+  const uint32_t lane = lane_id();
+  uint32_t lo = 0, len = n;
+  while (len > 1) {
+    const uint32_t step = (len + 63) >> 6, at = lane * step;
+    const uint64_t le = __ballot(at < len && v[lo + min(at, len - 1)] <= g);   // a prefix: v is sorted
+    const uint32_t k = (uint32_t)__popcll(le) - 1;                             // v[lo] <= g
+    lo += k * step;
+    len = min(step, len - k * step);
+  }
+  return lo;
+}
+
+// n bytes from src to dst by one wave, any alignment: 16-byte stores aligned
+// in dst (the loads need no alignment), up to 15 bytes at each end one by one.
+// All loads of a 4 KiB round go out before its stores.
+__device__ __forceinline__ void wave_copy(uint8_t* dst, const uint8_t* src, uint32_t n) {
+  const uint32_t lane = lane_id();
+  const uint32_t head = min(n, (uint32_t)(-(uintptr_t)dst & 15u));
+  const uint32_t n16 = (n - head) >> 4, t0 = head + 16 * n16;
+  const bool hb = lane < head, tb = t0 + lane < n;
+  const uint8_t h = hb ? src[lane] : (uint8_t)0, t = tb ? src[t0 + lane] : (uint8_t)0;
+  u32x4* d4 = reinterpret_cast<u32x4*>(dst + head);
+  for (uint32_t c = 0; c < n16; c += 256) {
+    u32x4 v[4] = {};
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++) {
+      const uint32_t i = c + 64 * u + lane;
+      if (i < n16) v[u] = ld128(src + head + 16 * (uint64_t)i);
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 4; u++) {
+      const uint32_t i = c + 64 * u + lane;
+      if (i < n16) d4[i] = v[u];
+    }
+  }
+  if (hb) dst[lane] = h;
+  if (tb) dst[t0 + lane] = t;
+}
+
+// Requested parts of blocks that were decoded into scratch slots, copied to
+// the output: one wave per part of a (request, covering block) pair, `parts`
+// parts to a block.  Bound by memory, so what counts is enough bytes in
+// flight: a grid sized by the bytes asked for (one workgroup per 256 blocks of
+// the file, a byte a thread, was 1506 us for 48 MiB of misaligned range).
+__global__ void __launch_bounds__(256) k_req_gather(ReqArgs R, uint32_t parts) {
   const uint64_t pairs = *ctl64(R.ctl, kCtlPairs);
   const uint32_t nreq = R.ctl[kCtlNReq];
-  const uint64_t B = 1ull << R.bl;
-  for (uint64_t g = blockIdx.x; g < pairs; g += gridDim.x) {
-    const uint32_t j = find_req(R.cnt_ptr, nreq, g);
+  const uint64_t B = 1ull << R.bl, P = B / parts, waves = (uint64_t)gridDim.x * 4;
+  for (uint64_t w = (uint64_t)blockIdx.x * 4 + uni(threadIdx.x >> 6); w < pairs * parts; w += waves) {
+    const uint64_t g = w / parts;
+    const uint32_t j = find_req_wave(R.cnt_ptr, nreq, g);
     const uint64_t s = R.spans[2 * j], e = R.spans[2 * j + 1];
     const uint64_t b = (s >> R.bl) + (g - R.cnt_ptr[j]);
     const uint64_t a = R.addr[b];
     if (!a) continue;
-    const uint64_t sb = b << R.bl, eb = min(sb + B, R.n);
-    const uint64_t lo = max(sb, s), hi = min(eb, e);
+    const uint64_t sb = b << R.bl, p0 = sb + (w - g * parts) * P;
+    const uint64_t lo = max(p0, s), hi = min(min(p0 + P, R.n), e);
     if (hi <= lo) continue;
     uint8_t* dst = R.out + R.offs[j] + (lo - s);
     const uint8_t* src = reinterpret_cast<const uint8_t*>(a) + (lo - sb);
     if (src == dst) continue;   // decoded in place
-    for (uint64_t q = threadIdx.x; q < hi - lo; q += blockDim.x) dst[q] = src[q];
+    wave_copy(dst, src, (uint32_t)(hi - lo));
   }
 }
 
@@ -2088,6 +2139,13 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
       hipLaunchKernelGGL(k_decode, dim3(grid), dim3(kWG), 0, s, A);
     }
   }
-  hipLaunchKernelGGL(k_req_gather, dim3(g_wide), dim3(256), 0, s, R);
+  // gather: a wave copies up to a quarter of a block (4 KiB in flight); records
+  // are short, so a wave takes what a record has in a block
+  const uint32_t parts = R.mode == 1 || Bs < 256 ? 1u : 4u;
+  const uint64_t pairs = R.mode == 0 ? single_len / Bs + 2
+                       : R.mode == 1 ? n_max * (v.max_record_len / Bs + 2)
+                                     : std::min<uint64_t>(cap / Bs, v.n_blocks * n_max) + 2 * n_max;
+  const uint64_t g_gather = (pairs * parts + 3) / 4;
+  hipLaunchKernelGGL(k_req_gather, dim3((uint32_t)std::min<uint64_t>(g_gather, 16ull * h->n_cu)), dim3(256), 0, s, R, parts);
   return launch_ok("request decode");
 }
