@@ -69,10 +69,12 @@ constexpr uint32_t kPrepRing = kWaves * 256 * 6;  // bytes of the two literal ri
 #define CLK_NOW() 0ull
 #endif
 
-// All LDS is static (52,832 B: three workgroups per CU).
+// All LDS is static: 53,568 B.  Three workgroups per CU need at most 53,760 B
+// each (LDS is handed out in pieces of 1,280 B, 128 per CU).
 struct Smem {
   uint32_t lut[kLutLit];       // literal decode entries: symbol | f << 8 | (slot - c) << 20
-  alignas(16) uint8_t tile[kB];// output tile; until stage 3 a copy of the payload prefix
+  alignas(16) uint8_t tile[kB + 16];   // output tile (16-byte reads may start at its last
+                               // byte); until stage 3 a copy of the payload prefix
   uint16_t cum[3][257];        // CMD, MLEN, OFF cumulative frequencies
   uint8_t bkt[3][256];         // per stream: symbol owning the first slot of each bucket
   uint16_t lit[kMaxSeq + 1];   // LL, then literal start of each sequence ([ns] = n_lit);
@@ -93,13 +95,17 @@ struct Smem {
     alignas(16) uint8_t prep[kPrepRing];   // between literal stages: the next block's
                                            // payload prefix (prep_ring)
   };
-  uint16_t fdst[64], flen[64], frng[64];   // at most 64 in-block matches: destination,
-  uint32_t fpk[64];                        // length, dependency range, source | period
+  union {
+    struct {
+      uint16_t fdst[64], flen[64], frng[64]; // at most 64 in-block matches: destination,
+      uint32_t fpk[64];                      // length, dependency range, source | period
+    };
+    uint64_t rdy[64];          // once those are in registers: the matches a pass copies
+  };                           // (destination | length << 16 | source << 32)
   uint32_t pst[7];             // literal record of the prepared block
   uint32_t pdir[4];            // its payload offset (low, high word), sequences, literals
   uint32_t plw[kWaves], pln[kWaves];   // its literal groups' first words and word counts
   uint32_t pok;                // prepared block: records valid
-  uint32_t dummy[64];          // target of the masked-off lanes' byte stores
   uint32_t scan[3][kWaves];
   uint32_t perr[3];            // prepared block: short stream k failed its checks
   uint32_t item, err, next, nin;
@@ -132,10 +138,39 @@ __device__ __forceinline__ uint64_t ld64(const uint8_t* p) {
   return (uint64_t)ld32(p) | ((uint64_t)ld32(p + 4) << 32);
 }
 
-// 16 bytes from any address (one load: the device takes unaligned ones)
+// Loads and stores at any address, in global memory and in LDS (one access
+// each: the device takes unaligned ones)
 typedef uint32_t u32x4 __attribute__((vector_size(16)));
-struct __attribute__((packed)) Any128 { u32x4 v; };
-__device__ __forceinline__ u32x4 ld128(const uint8_t* p) { return reinterpret_cast<const Any128*>(p)->v; }
+typedef uint32_t u32x2 __attribute__((vector_size(8)));
+template <class T> struct __attribute__((packed)) Any { T v; };
+template <class T> __device__ __forceinline__ T ld_any(const uint8_t* p) { return reinterpret_cast<const Any<T>*>(p)->v; }
+template <class T> __device__ __forceinline__ void st_any(uint8_t* p, T v) { reinterpret_cast<Any<T>*>(p)->v = v; }
+__device__ __forceinline__ u32x4 ld128(const uint8_t* p) { return ld_any<u32x4>(p); }
+// the first n <= 16 bytes of v to p
+__device__ __forceinline__ void st_upto16(uint8_t* p, u32x4 v, uint32_t n) {
+  if (n == 16) {
+    st_any<u32x4>(p, v);
+    return;
+  }
+  uint32_t a = v[0], b = v[1];
+  if (n & 8) {
+    st_any<u32x2>(p, (u32x2){a, b});
+    p += 8;
+    a = v[2];
+    b = v[3];
+  }
+  if (n & 4) {
+    st_any<uint32_t>(p, a);
+    p += 4;
+    a = b;
+  }
+  if (n & 2) {
+    st_any<uint16_t>(p, (uint16_t)a);
+    p += 2;
+    a >>= 16;
+  }
+  if (n & 1) *p = (uint8_t)a;
+}
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 // 16 bytes per lane straight from global memory into LDS, without registers
@@ -715,6 +750,53 @@ __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b)
   }
 }
 
+// n bytes of the tile from src to dst by one wave, not overlapping: 16 bytes a
+// lane at any alignment, 2 KiB of loads before their stores.
+__device__ __forceinline__ void tile_copy(Smem& S, uint32_t dst, uint32_t src, uint32_t n) {
+  const uint32_t o = 16 * lane_id();
+  for (uint32_t c = 0; c < n; c += 2048) {
+    u32x4 v[2] = {};
+#pragma unroll
+    for (uint32_t u = 0; u < 2; u++)
+      if (c + 1024 * u + o < n) v[u] = ld128(S.tile + src + c + 1024 * u + o);
+#pragma unroll
+    for (uint32_t u = 0; u < 2; u++) {
+      const uint32_t k = c + 1024 * u + o;
+      if (k < n) st_upto16(S.tile + dst + k, v[u], min(16u, n - k));
+    }
+  }
+}
+
+// In-block match of M bytes to tile position d0 from s = d0 - d (s < 0: its
+// first bytes lie in earlier blocks), by one wave: the d (or M) bytes before
+// the match repeats itself are copied, then what is there is appended to
+// itself, doubling, until M bytes stand.  A match that fills its block with
+// period 2 takes 14 steps (about 2 us); byte by byte, 64 at a time and each
+// step waiting for the one before, it was 27 us of a block's 55.
+__device__ __forceinline__ void copy_long(Smem& S, const DevArgs& A, uint64_t sb, uint32_t d0, uint32_t M,
+                                          int32_t s, uint32_t d, bool& bad) {
+  const uint32_t lane = lane_id();
+  const uint32_t n = min(d, M), n0 = s < 0 ? min(n, (uint32_t)-s) : 0u;
+  for (uint32_t c = 0; c < n0; c += 512) {          // from earlier blocks, eight loads in flight
+    uint32_t v[8];
+#pragma unroll
+    for (uint32_t u = 0; u < 8; u++) {
+      const uint32_t k = c + 64 * u + lane;
+      v[u] = k < n0 ? src_byte(A, sb + (int64_t)s + k, bad) : 0u;
+    }
+#pragma unroll
+    for (uint32_t u = 0; u < 8; u++) {
+      const uint32_t k = c + 64 * u + lane;
+      if (k < n0) S.tile[d0 + k] = (uint8_t)v[u];
+    }
+  }
+  if (n > n0) tile_copy(S, d0 + n0, (uint32_t)(s + (int32_t)n0), n - n0);
+  for (uint32_t f = n; f < M; f += min(f, M - f)) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // reads what was written
+    tile_copy(S, d0 + f, d0, min(f, M - f));
+  }
+}
+
 // Decode block b, prepared by prep_tile or prep_ring (S.pok, S.pst and the
 // sequence tables hold its stages 0 and 1), into the LDS tile and store it.
 // nb is the workgroup's next block or ~0u; the result is true when nb has
@@ -1044,29 +1126,30 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     bool bad = false;
-    // whole-wave copy of in-block match a (any length, period and source)
-    auto copy_match = [&](uint32_t a) {
-      const uint32_t pk = Fp[a];
-      const uint32_t d0 = Fd[a], M = Fl[a];
-      const int32_t s = (int32_t)(pk & 0xFFFFu) - 16384;
-      const uint32_t d = (pk >> 16) & 0x7FFFu;
-      // (k mod d) kept incrementally (a division only for d < 64)
-      uint32_t r = d >= M ? lane : (d >= 64 ? lane : lane % d);
-      const uint32_t r64 = d >= M ? 64u : (d >= 64 ? 64u : 64u % d);
-      for (uint32_t c = 0; c < M; c += 64) {
-        const uint32_t k = c + lane;
-        if (k < M && d0 + k < blen) {
-          const int32_t src = s + (int32_t)r;
-          const uint32_t v = src >= 0 ? (uint32_t)S.tile[(uint32_t)src & (kB - 1)]
-                                      : src_byte(A, sb + (int64_t)src, bad);
-          S.tile[d0 + k] = (uint8_t)v;
-        }
-        r += r64;
-        if (d < M && r >= d) r -= d;
+    // whole-wave copy of an in-block match (any length, period and source;
+    // uniform arguments): a short repeating one a byte per lane, the rest in
+    // longer pieces
+    auto copy_match = [&](uint32_t d0, uint32_t M, int32_t s, uint32_t d) {
+      if (M > 256 || d >= M || s < 0) {
+        copy_long(S, A, sb, d0, M, s, d, bad);
+        return;
+      }
+      // byte k of the match is byte k mod d of its source; k and d are below
+      // 256, so (k + 1/2) / d lies at least 1/510 away from any whole number,
+      // further than the float product is off
+      const float rd = 1.0f / (float)d;
+      uint32_t v[4];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++) {
+        const uint32_t k = 64 * u + lane;
+        if (64 * u < M) v[u] = S.tile[(uint32_t)s + k - d * (uint32_t)(((float)k + 0.5f) * rd)];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++) {
+        const uint32_t k = 64 * u + lane;
+        if (k < M) S.tile[d0 + k] = (uint8_t)v[u];
       }
     };
-    uint8_t* dummy = reinterpret_cast<uint8_t*>(&S.dummy[lane]);
-    const uint32_t* tw = reinterpret_cast<const uint32_t*>(S.tile);
     for (uint32_t c0 = 0; c0 < cnt; c0 += 64) {
       const uint32_t a = c0 + lane;
       const bool have = a < cnt;
@@ -1086,26 +1169,22 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
         const uint64_t m = __ballot(ready);
         if (!m) break;
         CLK_ADD(S, 10, 1);
-        const bool rf = ready && fast;
-        if (__ballot(rf)) {
-          // source words covering [s, s + len), realigned to the source start
-          const uint32_t w0 = (uint32_t)max(s, 0) >> 2, o = (uint32_t)max(s, 0) & 3u;
-          uint32_t Wd[kFastLen / 4 + 1];
-#pragma unroll
-          for (uint32_t i = 0; i < kFastLen / 4 + 1; i++) Wd[i] = tw[min(w0 + i, kB / 4 - 1)];
-          uint32_t Al[kFastLen / 4];
-#pragma unroll
-          for (uint32_t i = 0; i < kFastLen / 4; i++) Al[i] = __builtin_amdgcn_alignbyte(Wd[i + 1], Wd[i], o);
-          const uint32_t lim = rf ? len : 0u;
-#pragma unroll
-          for (uint32_t g = 0; g < kFastLen / 4; g++) {
-            if (!__ballot(4 * g < lim)) break;
-#pragma unroll
-            for (uint32_t u = 0; u < 4; u++) {
-              const uint32_t k = 4 * g + u;
-              uint8_t* p = k < lim ? S.tile + dst + k : dummy + u;
-              *p = (uint8_t)(Al[g] >> (8 * u));
-            }
+        const uint64_t mf = __ballot(ready && fast);
+        if (mf) {
+          // the ready matches side by side, then sixteen at a time, four lanes
+          // a match, each lane its 16 bytes: a pass has about ten ready matches
+          // of some 20 bytes, so one lane a match (17 words read, up to 64
+          // byte stores) left most lanes idle behind the longest match
+          if (ready && fast) S.rdy[mbcnt(mf)] = (uint64_t)(dst | (len << 16)) | ((uint64_t)(uint32_t)s << 32);
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          const uint32_t n = (uint32_t)__popcll(mf), sub = 16 * (lane & 3);
+          for (uint32_t g0 = 0; g0 < n; g0 += 16) {
+            const uint32_t i = g0 + (lane >> 2);
+            const uint64_t q = S.rdy[min(i, n - 1)];
+            const uint32_t L = (uint32_t)q >> 16;
+            const uint32_t lim = i < n && L > sub ? min(16u, L - sub) : 0u;
+            const uint32_t sa = lim ? (uint32_t)(q >> 32) + sub : 0u;
+            st_upto16(S.tile + ((uint32_t)q & 0xFFFFu) + sub, ld128(S.tile + sa), lim);
           }
         }
         uint64_t slow = __ballot(ready && !fast);
@@ -1114,7 +1193,9 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
         while (slow) {                        // wave-uniform
           const uint32_t l = (uint32_t)__builtin_ctzll(slow);
           slow &= slow - 1;
-          copy_match(c0 + l);
+          const uint32_t k = __builtin_amdgcn_readlane(pk, l);
+          copy_match(__builtin_amdgcn_readlane(dst, l), __builtin_amdgcn_readlane(len, l),
+                     (int32_t)(k & 0xFFFFu) - 16384, (k >> 16) & 0x7FFFu);
         }
         CLK_ADD(S, 12, CLK_NOW() - c1_);
         pending = pending && !ready;
