@@ -493,6 +493,27 @@ __device__ __forceinline__ uint32_t src_byte(const DevArgs& A, uint64_t a, bool&
   return reinterpret_cast<const uint8_t*>(base)[a & ((1ull << A.bl) - 1)];
 }
 
+// Sixteen source bytes from position a (all in earlier blocks).  In request
+// mode two blocks at most, whose decoded bytes may lie anywhere: bytes on both
+// sides of the block edge are fetched one by one.
+__device__ __forceinline__ u32x4 src16(const DevArgs& A, uint64_t a, bool& bad) {
+  if (!A.addr) return ld128(A.out + a);
+  const uint64_t base = A.addr[a >> A.bl], in = a & ((1ull << A.bl) - 1);
+  if (!base) {
+    bad = true;
+    return u32x4{};
+  }
+  if (in + 16 <= (1ull << A.bl)) return ld128(reinterpret_cast<const uint8_t*>(base) + in);
+  u32x4 v = {};
+#pragma unroll 1
+  for (uint32_t k = 0; k < 16; k++) {
+    const uint32_t x = src_byte(A, a + k, bad) << (8 * (k & 3));
+#pragma unroll
+    for (uint32_t w = 0; w < 4; w++) v[w] |= w == (k >> 2) ? x : 0u;
+  }
+  return v;
+}
+
 // Inclusive scan over the 64 lanes of a wave with DPP moves (no LDS): shifts
 // by 1, 2, 4 and 8 inside each 16-lane row, then the last lane of row 0 is
 // added to row 1 and of row 2 to row 3 (row_bcast:15), then lane 31 to rows
@@ -909,35 +930,37 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
   // ---- stage 3: literals straight to their tile positions; external matches
   {
     bool bad = false;
-    const uint32_t nx = min(S.next, ns), slot = lane >> 3, sub = lane & 7;
-    // Matches with a source wholly in earlier blocks.  In whole-file mode the
-    // first sixteen are started before the literal decode, four per wave (one
-    // per 16-lane quarter): each lane loads two aligned source words covering
-    // eight bytes of the match's first 128, so the HBM latency is spent
-    // decoding; the bytes are stored after it.  The rest are copied eight per
-    // wave at a time, one per 8-lane slot, each lane every eighth byte, all
-    // loads in flight before the stores.
-    const bool early = A.addr == nullptr;
-    const uint32_t quarter = lane >> 4, qsub = lane & 15;
-    uint32_t pM = 0, pd0 = 0, pw0 = 0, pw1 = 0;
-    uint64_t pof = 0, pa = 0;
-    if (early) {
-      const uint32_t e = 4 * wv + quarter;
+    // Matches with a source wholly in earlier blocks, four lanes a match, 16
+    // bytes a lane at any alignment.  Of a match of 16 bytes or more the last
+    // piece is moved back to end with the match (its overlap is written twice
+    // with the same bytes), so every access is whole and inside the source.
+    // The first 128 bytes of the first 64 matches are loaded before the literal
+    // decode and stored after it, so that their latency is spent decoding.
+    const uint32_t nx = min(S.next, ns), slot = t >> 2, sub = 16 * (t & 3);
+    struct Ext {
+      u32x4 v, w;           // bytes sub .. and 64 + sub ..
+      uint32_t M, d0;       // match length, destination
+      uint64_t of;          // source
+    };
+    auto ext_fields = [&](uint32_t e, Ext& x) {
       const uint32_t q = e < nx ? min((uint32_t)S.lst[e], ns - 1) : 0u;
       const uint32_t L = (uint32_t)S.lit[q + 1] - S.lit[q];
-      pM = e < nx ? (uint32_t)S.out[q + 1] - S.out[q] - L : 0u;
-      pof = (uint64_t)S.oflo[q] | ((uint64_t)S.ofhi[q] << 32);
-      pd0 = S.out[q] + L;
-      // words [pa, pa + 8) with pa = (of & ~3) + 8 * qsub cover the bytes
-      // k < 128 - (of & 3) of the match; the last word may reach up to 3 bytes
-      // past the match, still inside the output (the source ends at or
-      // before this block's start)
-      pa = (pof & ~3ull) + 8ull * qsub;
-      const uint32_t* w = reinterpret_cast<const uint32_t*>(A.out + pa);
-      const uint64_t lim = pof + min(pM, 128u - (uint32_t)(pof & 3));
-      pw0 = pa < lim ? w[0] : 0u;
-      pw1 = pa + 4 < lim ? w[1] : 0u;
-    }
+      x.M = e < nx ? (uint32_t)S.out[q + 1] - S.out[q] - L : 0u;
+      x.d0 = S.out[q] + L;
+      x.of = (uint64_t)S.oflo[q] | ((uint64_t)S.ofhi[q] << 32);
+    };
+    auto ext_load = [&](uint32_t e, Ext& x) {
+      ext_fields(e, x);
+      if (x.M >= 16 && sub < x.M) x.v = src16(A, x.of + min(sub, x.M - 16), bad);
+      if (64 + sub < x.M) x.w = src16(A, x.of + min(64 + sub, x.M - 16), bad);
+    };
+    auto ext_store = [&](const Ext& x) {
+      if (x.M >= 16 && sub < x.M) st_any<u32x4>(S.tile + x.d0 + min(sub, x.M - 16), x.v);
+      if (64 + sub < x.M) st_any<u32x4>(S.tile + x.d0 + min(64 + sub, x.M - 16), x.w);
+    };
+    Ext first;
+    first.v = first.w = u32x4{};
+    ext_load(slot, first);
     if (wv < Glit) {
       const uint32_t g = wv;
       bool okg;
@@ -963,52 +986,46 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
       }
     }
     CLK_MARK(S, 4);
-    if (early) {
-      const uint64_t lim = pof + min(pM, 128u - (uint32_t)(pof & 3));
-#pragma unroll
-      for (uint32_t u = 0; u < 8; u++) {
-        const uint64_t a = pa + u;
-        const uint32_t v = (u < 4 ? pw0 : pw1) >> (8 * (u & 3));
-        if (a >= pof && a < lim) S.tile[pd0 + (uint32_t)(a - pof)] = (uint8_t)v;
-      }
-      for (uint32_t k0 = 128u - (uint32_t)(pof & 3); __ballot(k0 < pM); k0 += 128) {   // the rest
-        uint32_t v[8];
-        const uint8_t* p = A.out + pof + k0 + qsub;
-#pragma unroll
-        for (uint32_t u = 0; u < 8; u++) v[u] = k0 + qsub + 16 * u < pM ? (uint32_t)p[16 * u] : 0u;
-#pragma unroll
-        for (uint32_t u = 0; u < 8; u++) {
-          const uint32_t k = k0 + qsub + 16 * u;
-          if (k < pM && pd0 + k < blen) S.tile[pd0 + k] = (uint8_t)v[u];
-        }
-      }
+    ext_store(first);
+    for (uint32_t e = 64 + slot; __ballot(e < nx); e += 64) {
+      Ext x;
+      x.v = x.w = u32x4{};
+      ext_load(e, x);
+      ext_store(x);
     }
-    for (uint32_t g0 = 8 * wv + (early ? 4 * kWaves : 0u); g0 < nx; g0 += 8 * kWaves) {
-      const uint32_t e = g0 + slot;
-      const uint32_t q = e < nx ? min((uint32_t)S.lst[e], ns - 1) : 0u;
-      const uint32_t L = (uint32_t)S.lit[q + 1] - S.lit[q];
-      const uint32_t M = e < nx ? (uint32_t)S.out[q + 1] - S.out[q] - L : 0u;
-      const uint64_t of = (uint64_t)S.oflo[q] | ((uint64_t)S.ofhi[q] << 32);
-      const uint32_t d0 = S.out[q] + L;
-      for (uint32_t k0 = 0; __ballot(k0 < M); k0 += 256) {
-        uint32_t v[32];
-        if (!A.addr) {                       // whole-file output: one base, byte offsets
-          const uint8_t* p = A.out + of + k0 + sub;
+    // what is left: matches longer than 128 bytes, four lanes up to 1 KiB, the
+    // whole wave beyond, and matches of less than 16 bytes byte by byte
+    for (uint32_t e = slot; __ballot(e < nx); e += 64) {
+      Ext x;
+      ext_fields(e, x);
+      const uint32_t mid = x.M <= 1024 ? x.M : 0u;
+      for (uint32_t k0 = 128 + sub; __ballot(k0 < mid); k0 += 256) {
+        u32x4 v[4] = {};
 #pragma unroll
-          for (uint32_t u = 0; u < 32; u++) v[u] = k0 + sub + 8 * u < M ? (uint32_t)p[8 * u] : 0u;
-        } else {
+        for (uint32_t u = 0; u < 4; u++)
+          if (k0 + 64 * u < mid) v[u] = src16(A, x.of + min(k0 + 64 * u, mid - 16), bad);
 #pragma unroll
-          for (uint32_t u = 0; u < 32; u++) {
-            const uint32_t k = k0 + sub + 8 * u;
-            v[u] = k < M ? src_byte(A, of + k, bad) : 0u;
-          }
-        }
+        for (uint32_t u = 0; u < 4; u++)
+          if (k0 + 64 * u < mid) st_any<u32x4>(S.tile + x.d0 + min(k0 + 64 * u, mid - 16), v[u]);
+      }
+      for (uint64_t big = __ballot(x.M > 1024 && sub == 0); big; big &= big - 1) {     // wave-uniform
+        const uint32_t l = (uint32_t)__builtin_ctzll(big);
+        const uint32_t M = __builtin_amdgcn_readlane(x.M, l), d0 = __builtin_amdgcn_readlane(x.d0, l);
+        const uint64_t of = (uint64_t)__builtin_amdgcn_readlane((uint32_t)x.of, l) |
+                            ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(x.of >> 32), l) << 32);
+        for (uint32_t c = 128 + 16 * lane; __ballot(c < M); c += 4096) {
+          u32x4 v[4] = {};
 #pragma unroll
-        for (uint32_t u = 0; u < 32; u++) {
-          const uint32_t k = k0 + sub + 8 * u;
-          if (k < M && d0 + k < blen) S.tile[d0 + k] = (uint8_t)v[u];
+          for (uint32_t u = 0; u < 4; u++)
+            if (c + 1024 * u < M) v[u] = src16(A, of + min(c + 1024 * u, M - 16), bad);
+#pragma unroll
+          for (uint32_t u = 0; u < 4; u++)
+            if (c + 1024 * u < M) st_any<u32x4>(S.tile + d0 + min(c + 1024 * u, M - 16), v[u]);
         }
       }
+      const uint32_t few = x.M < 16 ? x.M : 0u;
+      for (uint32_t k = t & 3; __ballot(k < few); k += 4)
+        if (k < few) S.tile[x.d0 + k] = (uint8_t)src_byte(A, x.of + k, bad);
     }
     if (bad) S.err = 1;
   }
@@ -1182,9 +1199,10 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
             const uint32_t i = g0 + (lane >> 2);
             const uint64_t q = S.rdy[min(i, n - 1)];
             const uint32_t L = (uint32_t)q >> 16;
-            const uint32_t lim = i < n && L > sub ? min(16u, L - sub) : 0u;
-            const uint32_t sa = lim ? (uint32_t)(q >> 32) + sub : 0u;
-            st_upto16(S.tile + ((uint32_t)q & 0xFFFFu) + sub, ld128(S.tile + sa), lim);
+            // the last piece of 16 bytes or more is moved back to end with the match
+            const uint32_t k = L >= 16 ? min(sub, L - 16) : 0u;
+            if (i < n && sub < L)
+              st_upto16(S.tile + ((uint32_t)q & 0xFFFFu) + k, ld128(S.tile + (uint32_t)(q >> 32) + k), min(L, 16u));
           }
         }
         uint64_t slow = __ballot(ready && !fast);
