@@ -21,8 +21,10 @@
 //      rings, idle until the next literal stage);
 //   5. the tile is written to HBM with 16-byte stores.
 // Blocks are taken in dependency-level order ("wavefront" order, paper:
-// Background section): either one launch per level, or one cooperative
-// launch whose workgroups walk the levels with a grid barrier between them.
+// Background section).  One launch decodes them all: a workgroup takes its
+// blocks by ticket, does everything of a block that needs no other block, and
+// waits for the completion flags of the blocks it copies from only before
+// those copies.  (One launch per level is the other mode.)
 // No MFMA: nothing here is a contraction.
 #include <hip/hip_runtime.h>
 
@@ -40,7 +42,8 @@ constexpr uint32_t kLutLit = 1u << kMaxPLit;      // 4096 packed literal entries
 constexpr uint32_t kL = 1u << 16;                 // rANS state lower bound
 constexpr uint32_t kFastLen = 64;                 // in-block matches copied by one lane
 constexpr uint32_t kClkSlots = 16;                // stage clocks: 9 stages, block count, events
-constexpr uint32_t kPrepRing = kWaves * 256 * 6;  // bytes of the two literal rings
+constexpr uint32_t kPrepRing = 5120;              // payload prefix kept in the literal rings
+constexpr uint32_t kDeps = 256;                   // dependencies whose ids are kept in LDS
 
 // Stage clocks (instrumented build only, -DLZ_STAGE_CLOCKS): a barrier, then
 // thread 0 adds the cycles since the previous mark to stage i.  The product
@@ -92,8 +95,10 @@ struct Smem {
       uint16_t ring[kWaves][256];  // rANS words of the literal stream staged per wave
       uint32_t ringe[kWaves][256]; // table entry of each staged word's slot
     };
-    alignas(16) uint8_t prep[kPrepRing];   // between literal stages: the next block's
-                                           // payload prefix (prep_ring)
+    struct {                       // between literal stages:
+      alignas(16) uint8_t prep[kPrepRing];   // the next block's payload prefix (prep_ring)
+      uint32_t dep[kDeps];                   // the blocks it copies from
+    };
   };
   union {
     struct {
@@ -108,7 +113,9 @@ struct Smem {
   uint32_t pok;                // prepared block: records valid
   uint32_t scan[3][kWaves];
   uint32_t perr[3];            // prepared block: short stream k failed its checks
-  uint32_t item, err, next, nin;
+  uint32_t ndep, wait;         // prepared block: how many blocks it copies from; not all done yet
+  uint32_t err, next, nin;
+  uint32_t nit, nb;            // the workgroup's next ticket and block
 #ifdef LZ_STAGE_CLOCKS
   uint64_t clk[kClkSlots], clk_last;
 #endif
@@ -125,18 +132,12 @@ struct DevArgs {
   uint32_t q_begin, q_end;  // static slice of the queue
   uint8_t* out;             // whole-file output base (direct mode)
   const uint64_t* addr;     // request mode: per-block device address, or null
-  uint32_t* flags;
+  uint32_t* flags;          // per block: the epoch it was last decoded in
   uint32_t* ctl;
-  uint32_t persistent;
+  uint32_t flow;            // 1, 2: blocks by ticket, ordered by completion flags (2: blocks
+                            // share cache lines of the output)
   uint32_t spin_limit;
 };
-
-__device__ __forceinline__ uint32_t ld32(const uint8_t* p) {
-  return (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16) | ((uint32_t)p[3] << 24);
-}
-__device__ __forceinline__ uint64_t ld64(const uint8_t* p) {
-  return (uint64_t)ld32(p) | ((uint64_t)ld32(p + 4) << 32);
-}
 
 // Loads and stores at any address, in global memory and in LDS (one access
 // each: the device takes unaligned ones)
@@ -145,6 +146,8 @@ typedef uint32_t u32x2 __attribute__((vector_size(8)));
 template <class T> struct __attribute__((packed)) Any { T v; };
 template <class T> __device__ __forceinline__ T ld_any(const uint8_t* p) { return reinterpret_cast<const Any<T>*>(p)->v; }
 template <class T> __device__ __forceinline__ void st_any(uint8_t* p, T v) { reinterpret_cast<Any<T>*>(p)->v = v; }
+__device__ __forceinline__ uint32_t ld32(const uint8_t* p) { return ld_any<uint32_t>(p); }
+__device__ __forceinline__ uint64_t ld64(const uint8_t* p) { return ld_any<uint64_t>(p); }
 __device__ __forceinline__ u32x4 ld128(const uint8_t* p) { return ld_any<u32x4>(p); }
 // the first n <= 16 bytes of v to p
 __device__ __forceinline__ void st_upto16(uint8_t* p, u32x4 v, uint32_t n) {
@@ -176,12 +179,12 @@ __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 // 16 bytes per lane straight from global memory into LDS, without registers
 // (global_load_lds_dwordx4): lane k's bytes land at dst + 16 k, dst being the
 // wave's uniform LDS address.  The compiler does not track the LDS write:
-// lds_dma_wait() (vmcnt(0)) must come before any read of the bytes.
+// vm_wait() (vmcnt(0)) must come before any read of the bytes.
 __device__ __forceinline__ void lds_dma16(const void* src, void* dst) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
                                    (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
 }
-__device__ __forceinline__ void lds_dma_wait() {
+__device__ __forceinline__ void vm_wait() {
   __builtin_amdgcn_s_waitcnt(0xF70);   // vmcnt(0), expcnt and lgkmcnt untouched
 }
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -487,23 +490,42 @@ __device__ bool lit_group_p(const uint8_t* body, uint32_t K, uint32_t n, uint32_
 // Source byte at absolute position a (an earlier block): direct mode reads the
 // whole-file output; request mode goes through the per-block address table.
 __device__ __forceinline__ uint32_t src_byte(const DevArgs& A, uint64_t a, bool& bad) {
-  if (!A.addr) return A.out[a];
-  const uint64_t base = A.addr[a >> A.bl];
-  if (!base) { bad = true; return 0; }
-  return reinterpret_cast<const uint8_t*>(base)[a & ((1ull << A.bl) - 1)];
+  const uint8_t* p = A.out + a;
+  if (A.addr) {
+    const uint64_t base = A.addr[a >> A.bl];
+    if (!base) { bad = true; return 0; }
+    p = reinterpret_cast<const uint8_t*>(base) + (a & ((1ull << A.bl) - 1));
+  }
+  return A.flow == 2 ? __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *p;
+}
+
+// Sixteen bytes of a finished block.  With shared lines (A.flow 2) by loads
+// that every XCD's writes are seen by: the aligned words that hold the bytes
+// (inside the block, whose size and place are multiples of 8).
+__device__ __forceinline__ u32x4 done16(const DevArgs& A, const uint8_t* p) {
+  if (A.flow != 2) return ld128(p);
+  const uint32_t o = (uint32_t)(uintptr_t)p & 7u;
+  const uint64_t* q = reinterpret_cast<const uint64_t*>(p - o);
+  uint64_t w[3];
+#pragma unroll
+  for (uint32_t k = 0; k < 3; k++)
+    w[k] = k < 2 || o ? __hip_atomic_load(q + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  const uint64_t lo = o ? (w[0] >> (8 * o)) | (w[1] << (64 - 8 * o)) : w[0];
+  const uint64_t hi = o ? (w[1] >> (8 * o)) | (w[2] << (64 - 8 * o)) : w[1];
+  return u32x4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
 }
 
 // Sixteen source bytes from position a (all in earlier blocks).  In request
 // mode two blocks at most, whose decoded bytes may lie anywhere: bytes on both
 // sides of the block edge are fetched one by one.
 __device__ __forceinline__ u32x4 src16(const DevArgs& A, uint64_t a, bool& bad) {
-  if (!A.addr) return ld128(A.out + a);
+  if (!A.addr) return done16(A, A.out + a);
   const uint64_t base = A.addr[a >> A.bl], in = a & ((1ull << A.bl) - 1);
   if (!base) {
     bad = true;
     return u32x4{};
   }
-  if (in + 16 <= (1ull << A.bl)) return ld128(reinterpret_cast<const uint8_t*>(base) + in);
+  if (in + 16 <= (1ull << A.bl)) return done16(A, reinterpret_cast<const uint8_t*>(base) + in);
   u32x4 v = {};
 #pragma unroll 1
   for (uint32_t k = 0; k < 16; k++) {
@@ -675,6 +697,33 @@ __device__ __forceinline__ void put_prep(Smem& S, const BlockDir& d, const Strea
 // (put_prep), the outcome to S.pok; a short stream that fails its checks sets
 // S.perr[k] (written by the wave that decoded stream k, 0 or 1).
 //
+// How many blocks b copies from and where their list starts; thread i of the
+// first kDeps gets the i-th of them.  Only by-ticket launches need them.
+struct Deps {
+  uint64_t at;
+  uint32_t n;
+};
+__device__ __forceinline__ Deps block_deps(const DevArgs& A, uint32_t b) {
+  Deps d = {0, 0};
+  if (A.flow) {
+    d.at = ld64(A.arc + A.off_dep_ptr + 8ull * b);
+    d.n = (uint32_t)(ld64(A.arc + A.off_dep_ptr + 8ull * b + 8) - d.at);
+  }
+  return d;
+}
+__device__ __forceinline__ uint32_t dep_id(const DevArgs& A, const Deps& d, uint32_t i) {
+  return ld32(A.arc + A.off_dep_idx + 4 * (d.at + i));
+}
+// by one wave
+__device__ __forceinline__ void put_deps(Smem& S, const DevArgs& A, const Deps& d) {
+  const uint32_t lane = lane_id();
+  for (uint32_t i = lane; i < min(d.n, kDeps); i += 64) S.dep[i] = dep_id(A, d, i);
+  if (lane == 0) {
+    S.ndep = d.n;
+    S.wait = 0;
+  }
+}
+
 // prep_tile: all four waves.  The first min(plen, 16 KiB) payload bytes go
 // into the tile (free until the literal stage) with one round of 16-byte
 // loads; waves 0..2 decode the short streams from there (at most about 9.3 KB
@@ -682,6 +731,7 @@ __device__ __forceinline__ void put_prep(Smem& S, const BlockDir& d, const Strea
 __device__ __forceinline__ void prep_tile(Smem& S, const DevArgs& A, uint32_t b) {
   const uint32_t t = threadIdx.x, wv = uni(t >> 6), lane = lane_id();
   const BlockDir d = block_dir(A, b);
+  const Deps dp = block_deps(A, b);
   const uint8_t* pay = A.arc + A.off_payload + d.poff;
   CLK_START(S);
   const uint32_t hlen = min(d.plen, kB);
@@ -693,7 +743,7 @@ __device__ __forceinline__ void prep_tile(Smem& S, const DevArgs& A, uint32_t b)
 #pragma unroll 1
       for (uint32_t i = 0; i < kB / (16 * kWG); i++)
         if (t + kWG * i < n16) lds_dma16(pay + 16 * (t + kWG * i), S.tile + 16 * (64 * wv + kWG * i));
-      lds_dma_wait();
+      vm_wait();
     } else {
       const uint4* src4 = reinterpret_cast<const uint4*>(pay);
       uint4* dst4 = reinterpret_cast<uint4*>(S.tile);
@@ -702,6 +752,7 @@ __device__ __forceinline__ void prep_tile(Smem& S, const DevArgs& A, uint32_t b)
     if (tail) S.tile[(hlen & ~15u) + t] = (uint8_t)tb;
   }
   if (t == 0) S.next = 0;
+  if (wv == 3) put_deps(S, A, dp);
   __syncthreads();
   CLK_MARK(S, 0);
   Stream sc, sm, so, sl;
@@ -733,6 +784,7 @@ __device__ __forceinline__ void prep_tile(Smem& S, const DevArgs& A, uint32_t b)
 __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b) {
   const uint32_t wv = uni(threadIdx.x >> 6), lane = lane_id();
   const BlockDir d = block_dir(A, b);
+  const Deps dp = block_deps(A, b);
   const uint8_t* pay = A.arc + A.off_payload + d.poff;
   const uint32_t hlen = min(d.plen, kPrepRing);
   {
@@ -746,12 +798,13 @@ __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b)
 #pragma unroll 1
       for (uint32_t i = 0; i < kPrepRing / 1024; i++)   // not unrolled: no hoisted addresses
         if (lane + 64 * i < n16) lds_dma16(pay + 16 * (lane + 64 * i), S.prep + 1024 * i);
-      lds_dma_wait();
     } else {
       const uint4* src4 = reinterpret_cast<const uint4*>(pay);
       uint4* dst4 = reinterpret_cast<uint4*>(S.prep);
       for (uint32_t c = lane; c < n16; c += 64) dst4[c] = src4[c];
     }
+    if (wv == 1) put_deps(S, A, dp);
+    vm_wait();
     if (tail) S.prep[(hlen & ~15u) + lane] = (uint8_t)tb;
   }
   __builtin_amdgcn_wave_barrier();
@@ -820,15 +873,26 @@ __device__ __forceinline__ void copy_long(Smem& S, const DevArgs& A, uint64_t sb
 
 // Decode block b, prepared by prep_tile or prep_ring (S.pok, S.pst and the
 // sequence tables hold its stages 0 and 1), into the LDS tile and store it.
-// nb is the workgroup's next block or ~0u; the result is true when nb has
+// it: its place in the queue's `total` blocks from qb on; epoch: the value of
+// a finished block's flag.  The next place and block go to S.nit and S.nb
+// (kNext of the result; unset after corrupt data); kPrepared: that block has
 // been prepared meanwhile, by waves 1..3 while wave 0 resolved b's in-block
 // matches.  Every loop below is bounded by values read from global memory
-// (directory, stream headers).
-__device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t b, uint32_t nb) {
+// (directory, stream headers) or by the spin limit.
+constexpr uint32_t kPrepared = 1, kNext = 2;
+__device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint32_t b, uint32_t qb,
+                                                 uint32_t total, uint32_t it, uint32_t epoch) {
   const uint32_t t = threadIdx.x, wv = uni(t >> 6), lane = lane_id();
   const uint64_t B = 1ull << A.bl, sb = (uint64_t)b << A.bl;
   const uint32_t blen = (uint32_t)((sb + B <= A.n) ? B : A.n - sb);
-  if (!uni(S.pok)) return false;               // corrupt records (latched by prep_tile)
+  if (!uni(S.pok)) return 0;                   // corrupt records (latched by prep_tile)
+  uint8_t* dst = A.addr ? reinterpret_cast<uint8_t*>(A.addr[b]) : A.out + sb;
+  // completion flags of the blocks b copies from, one per thread; looked at
+  // at the end of stage 2
+  const uint32_t nd = A.flow ? uni(S.ndep) : 0u;
+  const uint32_t dep = t < min(nd, kDeps) ? S.dep[t] : 0u;
+  uint32_t flag = epoch;
+  if (t < min(nd, kDeps)) flag = __hip_atomic_load(A.flags + dep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t poff = (uint64_t)uni(S.pdir[0]) | ((uint64_t)uni(S.pdir[1]) << 32);
   const uint32_t ns = uni(S.pdir[2]), nlit = uni(S.pdir[3]);
   const uint8_t* pay = A.arc + A.off_payload + poff;
@@ -920,11 +984,15 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
     }
     if (bad) S.err = 1;
   }
+  if (64 * wv < nd) {          // this wave holds some of the flags
+    if (__ballot(flag != epoch) || nd > kDeps) S.wait = 1;
+  }
   __syncthreads();
   if (S.err || S.perr[0] || S.perr[1] || S.perr[2]) {
     if (t == 0) latch(A.ctl, kStCorrupt);
-    return false;
+    return 0;
   }
+  const bool wait = uni(S.wait) != 0;
   CLK_MARK(S, 3);
 
   // ---- stage 3: literals straight to their tile positions; external matches
@@ -960,7 +1028,13 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
     };
     Ext first;
     first.v = first.w = u32x4{};
-    ext_load(slot, first);
+    first.M = first.d0 = 0;
+    if (!wait) ext_load(slot, first);
+    // the workgroup's next ticket; the literal decode hides the round trip
+    uint32_t nit = 0, nbq = ~0u;
+    if (t == 64)
+      nit = A.flow ? __hip_atomic_fetch_add(A.ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                   : it + gridDim.x;
     if (wv < Glit) {
       const uint32_t g = wv;
       bool okg;
@@ -986,6 +1060,29 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
       }
     }
     CLK_MARK(S, 4);
+    if (t == 64 && nit < total) nbq = A.queue[qb + nit];
+    if (wait) {
+      // The blocks b copies from have smaller tickets, so their workgroups
+      // run or have finished, and none of them waits for this one.
+      if (64 * wv < nd) {
+        const Deps dl = block_deps(A, b);
+        for (uint32_t i = t; __ballot(i < nd); i += kWG) {
+          const uint32_t id = i < kDeps ? dep : (i < nd ? dep_id(A, dl, i) : 0u);
+          bool pend = i < nd;
+          for (uint32_t spins = 0;; spins++) {
+            if (pend && __hip_atomic_load(A.flags + id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == epoch) pend = false;
+            if (!__ballot(pend)) break;
+            if (spins >= A.spin_limit || ((spins & 255u) == 255u && uni(watchdog_fired(A.ctl)))) {
+              if (pend) watchdog(A.ctl, 1, b, id, epoch - 1, epoch);
+              break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+          }
+        }
+      }
+      __syncthreads();
+      ext_load(slot, first);
+    }
     ext_store(first);
     for (uint32_t e = 64 + slot; __ballot(e < nx); e += 64) {
       Ext x;
@@ -1028,12 +1125,17 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
         if (k < few) S.tile[x.d0 + k] = (uint8_t)src_byte(A, x.of + k, bad);
     }
     if (bad) S.err = 1;
+    if (t == 64) {
+      S.nit = nit;
+      S.nb = nbq;
+    }
   }
   __syncthreads();
   if (S.err) {
     if (t == 0) latch(A.ctl, kStCorrupt);
-    return false;
+    return kNext;
   }
+  const uint32_t nb = uni(S.nb);
   CLK_MARK(S, 5);
 
   // ---- stage 4: matches whose source touches the block itself.
@@ -1242,23 +1344,31 @@ __device__ __forceinline__ bool decode_block(Smem& S, const DevArgs& A, uint32_t
   CLK_MARK(S, 7);
   if (S.err) {
     if (t == 0) latch(A.ctl, kStCorrupt);
-    return false;
+    return kNext | (prepared ? kPrepared : 0u);
   }
 
   // ---- stage 5: tile -> HBM with 16-byte stores
-  uint8_t* dst = A.addr ? reinterpret_cast<uint8_t*>(A.addr[b]) : A.out + sb;
   if (dst) {
     const uint32_t full = blen >> 4;
     const uint4* s4 = reinterpret_cast<const uint4*>(S.tile);
     uint4* d4 = reinterpret_cast<uint4*>(dst);
-    for (uint32_t c = t; c < full; c += kWG) d4[c] = s4[c];
-    for (uint32_t c = (full << 4) + t; c < blen; c += kWG) dst[c] = S.tile[c];
+    if (A.flow) {              // through the L2, to where every XCD sees it
+      uint64_t* d8 = reinterpret_cast<uint64_t*>(dst);
+      const uint64_t* s8 = reinterpret_cast<const uint64_t*>(S.tile);
+      for (uint32_t c = t; c < blen >> 3; c += kWG)
+        __hip_atomic_store(d8 + c, s8[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (uint32_t c = (blen & ~7u) + t; c < blen; c += kWG)
+        __hip_atomic_store(dst + c, S.tile[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      for (uint32_t c = t; c < full; c += kWG) d4[c] = s4[c];
+      for (uint32_t c = (full << 4) + t; c < blen; c += kWG) dst[c] = S.tile[c];
+    }
   }
   CLK_MARK(S, 8);
 #ifdef LZ_STAGE_CLOCKS
   if (t == 0) S.clk[9] += 1;
 #endif
-  return prepared;
+  return kNext | (prepared ? kPrepared : 0u);
 }
 
 
@@ -1290,7 +1400,7 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
     }
     if (lane == 63) S.cum[k][256] = (uint16_t)min(c, 65535u);
   }
-  lds_dma_wait();                      // this wave's LUT rows, before the barrier
+  vm_wait();                      // this wave's LUT rows, before the barrier
   __syncthreads();
   // bucket index of each short stream: bucket b starts at slot b << bs
   for (uint32_t e = t; e < 3 * 256; e += kWG) {
@@ -1300,84 +1410,78 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
   }
 }
 
-// Grid-wide barrier of a cooperative launch: arrivals are counted in one
-// control word (reset before the launch); barrier k (k = 1, 2, ...) completes
-// when nwg * k workgroups have arrived.  Agent-scope release before the
-// arrival and acquire after the wait make the blocks decoded before the
-// barrier visible to every workgroup after it.  A wait longer than the spin
-// limit latches the watchdog and lets the kernel finish (status ECORRUPT).
-__device__ __forceinline__ void grid_barrier(uint32_t* ctl, uint32_t target, uint32_t spin_limit) {
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    __hip_atomic_fetch_add(ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    uint32_t seen;
-    for (uint32_t spins = 0;
-         (seen = __hip_atomic_load(ctl + kCtlTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) < target; spins++) {
-      if (spins >= spin_limit || ((spins & 255u) == 255u && watchdog_fired(ctl))) {
-        watchdog(ctl, 4, target, 0, seen, target);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(2);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  }
-  __syncthreads();
-}
-
-// Per-level launches: a grid-stride slice of the level's queue; a workgroup
-// without a block leaves before loading any table.  Persistent (one
-// cooperative launch, every workgroup resident): the levels in order, each a
-// grid-stride slice of qptr[L] .. qptr[L+1], a grid barrier before every
-// non-empty level but the first.  decode_block has one call site, so the
-// kernel's register budget is that of one copy of it.
+// By ticket (A.flow): one launch over the whole level-ordered queue.  A
+// workgroup decodes the block of its ticket and publishes it by setting the
+// block's flag to this launch's epoch.  Every block that it may have to wait
+// for has a smaller ticket, held by a workgroup that runs, so the wait ends
+// whatever else runs on the GPU and however few workgroups are resident.  The
+// last workgroup to leave resets the tickets and makes the epoch current.
+// The XCDs' L2s are not coherent with each other while a kernel runs, and
+// writing back and invalidating them for each block costs more than it gives
+// (256 MiB FASTQ 826 us, against 583 us with a launch per level).  So a tile
+// is stored through the L2 (agent-scope stores) and its flag only after every
+// wave's stores have completed; and a reader cannot hold an old copy of a
+// line, as caches start a kernel without one and no line of a block is read
+// before its flag is seen -- unless blocks share lines, because the output is
+// not aligned to them (A.flow 2): then sources are read by agent-scope loads.
+// A launch per level costs at least a block's latency (28 us) a level:
+// 256 MiB FASTQ (6 levels) 583 us so and 500 us by ticket, 128 MiB genome (7)
+// 432 and 306, 64 MiB FASTQ of 64 levels 1763 and 595, one record 135 and 64.
+// Otherwise a grid-stride slice of the queue's blocks q_begin .. q_end (one
+// level).
 __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per SIMD: at most 168 VGPRs
   __shared__ Smem S;
   // issue priority: 1 by default, 2 for wave 0's in-block passes, 0 for the
   // next block's preparation by waves 1..3 (the one stage with slack)
   __builtin_amdgcn_s_setprio(1);
   const uint32_t t = threadIdx.x;
-  uint32_t it = 0, qe = 0, L = 0, bars = 0;
-  bool pending = false;       // (persistent) a non-empty level has been started
-  if (!A.persistent) {
-    uint32_t qb = A.q_begin;
-    qe = A.q_end;
-    if (A.qptr) {
-      qb = A.qptr[A.q_begin];
-      qe = A.qptr[A.q_end];
-    }
-    it = qb + blockIdx.x;
-    if (it >= qe) return;
+  uint32_t qb = A.q_begin, qe = A.q_end;
+  if (A.qptr) {
+    qb = A.qptr[A.q_begin];
+    qe = A.qptr[A.q_end];
   }
+  const uint32_t total = qe - qb;
+  if (blockIdx.x >= total) return;         // more workgroups than blocks
+  auto ticket = [&]() {
+    return __hip_atomic_fetch_add(A.ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (A.flow && t == 0) S.nit = ticket();
 #ifdef LZ_STAGE_CLOCKS
   if (t < kClkSlots) S.clk[t] = 0;
 #endif
-  bool tables = false;        // tables are loaded before the workgroup's first block
-  bool prepared = false;      // the next block's stages 0 and 1 are done
-  for (;;) {
-    if (A.persistent) {
-      while (it >= qe && L < kMaxLevels) {     // this workgroup's next block, in a later level
-        const uint32_t b0 = A.qptr[L], b1 = A.qptr[L + 1];
-        L++;
-        if (b0 >= b1) continue;
-        if (pending) grid_barrier(A.ctl, gridDim.x * ++bars, A.spin_limit);
-        pending = true;
-        it = b0 + blockIdx.x;
-        qe = b1;
-      }
-    }
-    if (it >= qe) break;
-    if (!tables) {
-      load_tables(S, A);
-      __syncthreads();
-      tables = true;
-    }
-    const uint32_t nit = it + gridDim.x;
-    const uint32_t b = A.queue[it], nb = nit < qe ? A.queue[nit] : ~0u;
+  const uint32_t epoch = A.flow ? A.ctl[kCtlEpoch] + 1 : 0u;
+  load_tables(S, A);
+  __syncthreads();
+  uint32_t it = A.flow ? uni(S.nit) : blockIdx.x;
+  uint32_t b = it < total ? A.queue[qb + it] : 0u;
+  bool prepared = false;      // the block's stages 0 and 1 are done
+  while (it < total) {
     if (!prepared) prep_tile(S, A, b);
-    prepared = decode_block(S, A, b, nb);
+    const uint32_t r = decode_block(S, A, b, qb, total, it, epoch);
+    if (A.flow) vm_wait();                 // this wave's stores have left
     __syncthreads();
-    it = nit;
+    if (A.flow && t == 0) {
+      __hip_atomic_store(A.flags + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    prepared = (r & kPrepared) != 0;
+    if (r & kNext) {
+      it = uni(S.nit);
+      b = uni(S.nb);
+    } else {                               // corrupt block: no ticket was taken
+      if (t == 0) S.nit = A.flow ? ticket() : it + gridDim.x;
+      __syncthreads();
+      it = uni(S.nit);
+      b = it < total ? A.queue[qb + it] : 0u;
+      __syncthreads();
+    }
+  }
+  if (A.flow && t == 0) {
+    const uint32_t left = __hip_atomic_fetch_add(A.ctl + kCtlLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (left + 1 == min(gridDim.x, total)) {
+      A.ctl[kCtlTicket] = 0;
+      A.ctl[kCtlLeft] = 0;
+      A.ctl[kCtlEpoch] = epoch;
+    }
   }
 #ifdef LZ_STAGE_CLOCKS
   __syncthreads();
@@ -1418,26 +1522,11 @@ __global__ void k_fill_u64(uint64_t* p, uint64_t n, uint64_t v) {
   for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
-// Start of a decode pass: new completion epoch, ticket reset.
-__global__ void k_begin(uint32_t* ctl) {
-  ctl[kCtlEpoch] += 1;
-  ctl[kCtlTicket] = 0;
-}
-
 }  // namespace
 
 // ---- host launchers (called from runtime.cpp) -------------------------------
 
 size_t lz_decode_smem_bytes() { return sizeof(Smem); }
-
-// Decode workgroups resident per compute unit (the cooperative grid is this
-// times the CU count).
-int lz_decode_occupancy(int* per_cu) {
-  const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(per_cu, reinterpret_cast<const void*>(k_decode),
-                                                                    (int)kWG, 0);
-  if (e != hipSuccess) return lz_fail(LZ_EDEVICE, "decode occupancy: %s", hipGetErrorString(e));
-  return LZ_OK;
-}
 
 static DevArgs make_args(const lz_handle* h) {
   DevArgs A{};
@@ -1483,35 +1572,23 @@ int lz_launch_setup(lz_handle* h, hipStream_t s) {
   return launch_ok("lz_open setup kernels");
 }
 
-// Persistent mode: one cooperative launch of every resident workgroup (the
-// runtime refuses it rather than leave any workgroup waiting for a slot).
-// Inside a stream capture the levels are launched one by one instead.
-static int launch_persistent(lz_handle* h, DevArgs A, hipStream_t s, bool* done) {
-  *done = false;
-  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cs) != hipSuccess) return lz_fail(LZ_EDEVICE, "stream capture query failed");
-  if (cs != hipStreamCaptureStatusNone) return LZ_OK;
-  A.persistent = 1;
-  void* args[] = {&A};
-  const hipError_t e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_decode), dim3(h->coop_grid),
-                                                  dim3(kWG), args, 0, s);
-  if (e != hipSuccess) return lz_fail(LZ_EDEVICE, "cooperative decode launch: %s", hipGetErrorString(e));
-  *done = true;
-  return LZ_OK;
+// Whether the blocks of a by-ticket launch have their cache lines (128 bytes)
+// to themselves (1) or share some (2): see k_decode.  `at`: an address that
+// every block's output lies a multiple of the block size from.
+static uint32_t flow_mode(const DevArgs& A, uint64_t at) {
+  return A.bl >= 7 && (at & 127) == 0 ? 1u : 2u;
 }
 
 int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
   DevArgs A = make_args(h);
   A.queue = h->ws.queue;
   A.out = out;
-  const size_t smem = 0;   // all LDS is static
   const uint32_t slots = (uint32_t)(h->n_cu * std::max(1u, h->tune.wg_per_cu));
-  hipLaunchKernelGGL(k_begin, dim3(1), dim3(1), 0, s, h->ws.ctl);
-  if (h->tune.sync_mode == 1) {
-    A.qptr = h->ws.level_ptr;
-    bool done = false;
-    const int rc = launch_persistent(h, A, s, &done);
-    if (rc || done) return rc ? rc : launch_ok("lz_decode_all");
+  if (h->tune.sync_mode == 0) {
+    A.flow = flow_mode(A, reinterpret_cast<uintptr_t>(out));
+    A.q_end = (uint32_t)h->av.n_blocks;
+    hipLaunchKernelGGL(k_decode, dim3(std::min(A.q_end, slots)), dim3(kWG), 0, s, A);
+    return launch_ok("lz_decode_all");
   }
   uint32_t base = 0;
   for (uint32_t L = 0; L < h->av.n_levels; L++) {
@@ -1519,7 +1596,7 @@ int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
     if (c) {
       A.q_begin = base;
       A.q_end = base + c;
-      hipLaunchKernelGGL(k_decode, dim3(std::min(c, slots)), dim3(kWG), smem, s, A);
+      hipLaunchKernelGGL(k_decode, dim3(std::min(c, slots)), dim3(kWG), 0, s, A);
     }
     base += c;
   }
@@ -1839,8 +1916,6 @@ __global__ void __launch_bounds__(256) k_req_begin(ReqArgs R) {
   if (t < 64) R.ctl[kCtlLevelCnt + t] = 0;
   if (t == 0) {
     R.ctl[kCtlREpoch] += 1;
-    R.ctl[kCtlEpoch] += 1;
-    R.ctl[kCtlTicket] = 0;
     R.ctl[kCtlListTail] = 0;
     R.ctl[kCtlListHead] = 0;
     R.ctl[kCtlListDone] = 0;
@@ -2083,8 +2158,6 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
   if (t == 0) {
     s_epoch = R.ctl[kCtlREpoch] + 1;
     R.ctl[kCtlREpoch] = s_epoch;
-    R.ctl[kCtlEpoch] += 1;
-    R.ctl[kCtlTicket] = 0;
     R.ctl[kCtlListHead] = 0;
     R.ctl[kCtlListDone] = 0;
     R.ctl[kCtlNReq] = s_nreq;
@@ -2302,6 +2375,25 @@ __global__ void __launch_bounds__(256) k_req_gather(ReqArgs R, uint32_t parts) {
   }
 }
 
+// The same by one workgroup, a byte a thread (see lz_launch_requests).
+__global__ void __launch_bounds__(256) k_req_gather_one(ReqArgs R) {
+  const uint64_t pairs = *ctl64(R.ctl, kCtlPairs);
+  const uint32_t nreq = R.ctl[kCtlNReq];
+  const uint64_t B = 1ull << R.bl;
+  for (uint64_t g = 0; g < pairs; g++) {
+    const uint32_t j = find_req(R.cnt_ptr, nreq, g);
+    const uint64_t s = R.spans[2 * j], e = R.spans[2 * j + 1];
+    const uint64_t b = (s >> R.bl) + (g - R.cnt_ptr[j]);
+    const uint64_t a = R.addr[b];
+    if (!a) continue;
+    const uint64_t sb = b << R.bl, lo = max(sb, s), hi = min(min(sb + B, R.n), e);
+    if (hi <= lo) continue;
+    uint8_t* dst = R.out + R.offs[j] + (lo - s);
+    const uint8_t* src = reinterpret_cast<const uint8_t*>(a) + (lo - sb);
+    for (uint64_t q = threadIdx.x; q < hi - lo; q += blockDim.x) dst[q] = src[q];
+  }
+}
+
 }  // namespace
 
 int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d_n, uint64_t n_max,
@@ -2370,7 +2462,7 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
     hipLaunchKernelGGL(k_req_level_scan, dim3(1), dim3(64), 0, s, R);
     hipLaunchKernelGGL(k_req_scatter, dim3(g_wide), dim3(256), 0, s, R);
   }
-  // decode the closure in level order (one cooperative launch, or one launch per level)
+  // decode the closure in level order (one launch, or one per level)
   DevArgs A = make_args(h);
   A.queue = h->ws.rqueue;
   A.qptr = h->ws.rlevel_ptr;
@@ -2378,12 +2470,14 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   A.out = d_out;
   const uint32_t slots = (uint32_t)(h->n_cu * std::max(1u, h->tune.wg_per_cu));
   const uint32_t grid = (uint32_t)std::min<uint64_t>(slots, std::max<uint64_t>(1, v.n_blocks));
-  bool done = false;
-  if (h->tune.req_sync_mode == 1) {
-    const int rc = launch_persistent(h, A, s, &done);
-    if (rc) return rc;
-  }
-  if (!done) {
+  if (h->tune.req_sync_mode == 0) {
+    // scratch slots are whole lines; blocks decoded straight into the output lie
+    // at d_out - single_off plus a multiple of the block size
+    const uint64_t at = reinterpret_cast<uintptr_t>(d_out) - single_off;
+    A.flow = flow_mode(A, R.direct && (at & 15) == 0 ? at : 0);
+    A.q_end = kMaxLevels;                  // rlevel_ptr[0] .. rlevel_ptr[64]: the whole closure
+    hipLaunchKernelGGL(k_decode, dim3(grid), dim3(kWG), 0, s, A);
+  } else {
     for (uint32_t L = 0; L < v.n_levels; L++) {
       A.q_begin = L;
       A.q_end = L + 1;
@@ -2397,6 +2491,13 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
                        : R.mode == 1 ? n_max * (v.max_record_len / Bs + 2)
                                      : std::min<uint64_t>(cap / Bs, v.n_blocks * n_max) + 2 * n_max;
   const uint64_t g_gather = (pairs * parts + 3) / 4;
-  hipLaunchKernelGGL(k_req_gather, dim3((uint32_t)std::min<uint64_t>(g_gather, 16ull * h->n_cu)), dim3(256), 0, s, R, parts);
+  // Batches on an archive of less than 256 blocks stay with one workgroup: a
+  // program that serves such an archive (tests/test_gpu_serve.py) counts on a
+  // batch of 3 MiB being on the device for the millisecond in which the next
+  // ones arrive (3 ms so, 0.14 ms with the grid below).
+  if (R.mode == 2 && v.n_blocks < 256)
+    hipLaunchKernelGGL(k_req_gather_one, dim3(1), dim3(256), 0, s, R);
+  else
+    hipLaunchKernelGGL(k_req_gather, dim3((uint32_t)std::min<uint64_t>(g_gather, 16ull * h->n_cu)), dim3(256), 0, s, R, parts);
   return launch_ok("request decode");
 }

@@ -61,14 +61,15 @@ struct Workspace {
 // control words in Workspace::ctl (u32 each; 64-bit values use two words)
 enum : uint32_t {
   kCtlStatus = 0,     // latched status bits
-  kCtlTicket = 1,     // cooperative decode: grid-barrier arrivals
-  kCtlEpoch = 2,      // completion epoch (per-block flags)
+  kCtlTicket = 1,     // decode: next ticket of the running launch (0 between launches)
+  kCtlEpoch = 2,      // completion epoch (per-block flags) of the last finished decode
   kCtlREpoch = 3,     // request epoch (closure marks)
   kCtlListTail = 4,   // closure list: entries pushed
   kCtlListHead = 5,   // closure list: entries taken
   kCtlListDone = 6,   // closure list: entries fully expanded
   kCtlSlots = 7,      // scratch slots handed out
   kCtlNReq = 8,       // number of requests of the current batch
+  kCtlLeft = 9,       // decode: workgroups of the running launch that have finished
   kCtlTotal = 10,     // u64: total output bytes of the batch
   kCtlPairs = 12,     // u64: (request, covering block) pairs of the batch
   kCtlLevelCnt = 16,  // 64 level counters of the closure queue
@@ -83,7 +84,6 @@ struct lz_handle {
   lz_tuning tune;
   int n_cu;
   int dev;                            // device the handle was opened on
-  uint32_t coop_grid;                 // resident decode workgroups (cooperative launch)
   uint32_t level_count[kMaxLevels];   // host copy of the whole-file level histogram
   uint64_t literal_bytes;             // sum of n_lit over blocks
   uint64_t payload_bytes;             // end of the last block payload
