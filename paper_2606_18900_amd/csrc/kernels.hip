@@ -113,7 +113,8 @@ struct Smem {
   uint32_t pok;                // prepared block: records valid
   uint32_t scan[3][kWaves];
   uint32_t perr[3];            // prepared block: short stream k failed its checks
-  uint32_t ndep, wait;         // prepared block: how many blocks it copies from; not all done yet
+  uint32_t ndep, wait, used;   // prepared block: how many blocks it copies from; not all done
+                               // yet; some block copies from it
   uint32_t err, next, nin;
   uint32_t nit, nb;            // the workgroup's next ticket and block
 #ifdef LZ_STAGE_CLOCKS
@@ -697,15 +698,16 @@ __device__ __forceinline__ void put_prep(Smem& S, const BlockDir& d, const Strea
 // (put_prep), the outcome to S.pok; a short stream that fails its checks sets
 // S.perr[k] (written by the wave that decoded stream k, 0 or 1).
 //
-// How many blocks b copies from and where their list starts; thread i of the
-// first kDeps gets the i-th of them.  Only by-ticket launches need them.
+// How many blocks b copies from, where their list starts, and whether any
+// block copies from b.  Only by-ticket launches need them.
 struct Deps {
   uint64_t at;
-  uint32_t n;
+  uint32_t n, used;
 };
 __device__ __forceinline__ Deps block_deps(const DevArgs& A, uint32_t b) {
-  Deps d = {0, 0};
+  Deps d = {0, 0, 0};
   if (A.flow) {
+    d.used = A.flags[b] != kFlagLeaf ? 1u : 0u;
     d.at = ld64(A.arc + A.off_dep_ptr + 8ull * b);
     d.n = (uint32_t)(ld64(A.arc + A.off_dep_ptr + 8ull * b + 8) - d.at);
   }
@@ -720,6 +722,7 @@ __device__ __forceinline__ void put_deps(Smem& S, const DevArgs& A, const Deps& 
   for (uint32_t i = lane; i < min(d.n, kDeps); i += 64) S.dep[i] = dep_id(A, d, i);
   if (lane == 0) {
     S.ndep = d.n;
+    S.used = d.used;
     S.wait = 0;
   }
 }
@@ -877,20 +880,25 @@ __device__ __forceinline__ void copy_long(Smem& S, const DevArgs& A, uint64_t sb
 // a finished block's flag.  The next place and block go to S.nit and S.nb
 // (kNext of the result; unset after corrupt data); kPrepared: that block has
 // been prepared meanwhile, by waves 1..3 while wave 0 resolved b's in-block
-// matches.  Every loop below is bounded by values read from global memory
+// matches; kUsed: other blocks may be waiting for this one.  Every loop below is bounded by values read from global memory
 // (directory, stream headers) or by the spin limit.
-constexpr uint32_t kPrepared = 1, kNext = 2;
+__device__ __forceinline__ uint32_t take_ticket(const DevArgs& A) {
+  return __hip_atomic_fetch_add(A.ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+constexpr uint32_t kPrepared = 1, kNext = 2, kUsed = 4;
 __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint32_t b, uint32_t qb,
                                                  uint32_t total, uint32_t it, uint32_t epoch) {
   const uint32_t t = threadIdx.x, wv = uni(t >> 6), lane = lane_id();
   const uint64_t B = 1ull << A.bl, sb = (uint64_t)b << A.bl;
   const uint32_t blen = (uint32_t)((sb + B <= A.n) ? B : A.n - sb);
-  if (!uni(S.pok)) return 0;                   // corrupt records (latched by prep_tile)
+  if (!uni(S.pok)) return kUsed;               // corrupt records (latched by prep_tile)
   uint8_t* dst = A.addr ? reinterpret_cast<uint8_t*>(A.addr[b]) : A.out + sb;
   // completion flags of the blocks b copies from, one per thread; looked at
   // at the end of stage 2
   const uint32_t nd = A.flow ? uni(S.ndep) : 0u;
   const uint32_t dep = t < min(nd, kDeps) ? S.dep[t] : 0u;
+  const bool used = A.flow && uni(S.used);
   uint32_t flag = epoch;
   if (t < min(nd, kDeps)) flag = __hip_atomic_load(A.flags + dep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t poff = (uint64_t)uni(S.pdir[0]) | ((uint64_t)uni(S.pdir[1]) << 32);
@@ -990,7 +998,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   __syncthreads();
   if (S.err || S.perr[0] || S.perr[1] || S.perr[2]) {
     if (t == 0) latch(A.ctl, kStCorrupt);
-    return 0;
+    return kUsed;
   }
   const bool wait = uni(S.wait) != 0;
   CLK_MARK(S, 3);
@@ -1032,9 +1040,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     if (!wait) ext_load(slot, first);
     // the workgroup's next ticket; the literal decode hides the round trip
     uint32_t nit = 0, nbq = ~0u;
-    if (t == 64)
-      nit = A.flow ? __hip_atomic_fetch_add(A.ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                   : it + gridDim.x;
+    if (t == 64) nit = A.flow ? take_ticket(A) : it + gridDim.x;
     if (wv < Glit) {
       const uint32_t g = wv;
       bool okg;
@@ -1133,7 +1139,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   __syncthreads();
   if (S.err) {
     if (t == 0) latch(A.ctl, kStCorrupt);
-    return kNext;
+    return kNext | kUsed;
   }
   const uint32_t nb = uni(S.nb);
   CLK_MARK(S, 5);
@@ -1344,7 +1350,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   CLK_MARK(S, 7);
   if (S.err) {
     if (t == 0) latch(A.ctl, kStCorrupt);
-    return kNext | (prepared ? kPrepared : 0u);
+    return kNext | kUsed | (prepared ? kPrepared : 0u);
   }
 
   // ---- stage 5: tile -> HBM with 16-byte stores
@@ -1352,7 +1358,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     const uint32_t full = blen >> 4;
     const uint4* s4 = reinterpret_cast<const uint4*>(S.tile);
     uint4* d4 = reinterpret_cast<uint4*>(dst);
-    if (A.flow) {              // through the L2, to where every XCD sees it
+    if (used) {                // through the L2, to where every XCD sees it
       uint64_t* d8 = reinterpret_cast<uint64_t*>(dst);
       const uint64_t* s8 = reinterpret_cast<const uint64_t*>(S.tile);
       for (uint32_t c = t; c < blen >> 3; c += kWG)
@@ -1368,7 +1374,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
 #ifdef LZ_STAGE_CLOCKS
   if (t == 0) S.clk[9] += 1;
 #endif
-  return kNext | (prepared ? kPrepared : 0u);
+  return kNext | (prepared ? kPrepared : 0u) | (used ? kUsed : 0u);
 }
 
 
@@ -1420,10 +1426,13 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
 // writing back and invalidating them for each block costs more than it gives
 // (256 MiB FASTQ 826 us, against 583 us with a launch per level).  So a tile
 // is stored through the L2 (agent-scope stores) and its flag only after every
-// wave's stores have completed; and a reader cannot hold an old copy of a
+// wave's stores have completed (both only if some block copies from it: of a
+// FASTQ a third of the blocks, of a genome a tenth); and a reader cannot hold an old copy of a
 // line, as caches start a kernel without one and no line of a block is read
 // before its flag is seen -- unless blocks share lines, because the output is
 // not aligned to them (A.flow 2): then sources are read by agent-scope loads.
+// (Tickets of two or four consecutive blocks, to take fewer, delay the blocks
+// that others wait for: 64 levels 1134 us instead of 600.)
 // A launch per level costs at least a block's latency (28 us) a level:
 // 256 MiB FASTQ (6 levels) 583 us so and 500 us by ticket, 128 MiB genome (7)
 // 432 and 306, 64 MiB FASTQ of 64 levels 1763 and 595, one record 135 and 64.
@@ -1442,10 +1451,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
   }
   const uint32_t total = qe - qb;
   if (blockIdx.x >= total) return;         // more workgroups than blocks
-  auto ticket = [&]() {
-    return __hip_atomic_fetch_add(A.ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  };
-  if (A.flow && t == 0) S.nit = ticket();
+  if (A.flow && t == 0) S.nit = take_ticket(A);
 #ifdef LZ_STAGE_CLOCKS
   if (t < kClkSlots) S.clk[t] = 0;
 #endif
@@ -1458,9 +1464,10 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
   while (it < total) {
     if (!prepared) prep_tile(S, A, b);
     const uint32_t r = decode_block(S, A, b, qb, total, it, epoch);
-    if (A.flow) vm_wait();                 // this wave's stores have left
+    const bool publish = A.flow && (r & kUsed);
+    if (publish) vm_wait();                // this wave's stores have completed
     __syncthreads();
-    if (A.flow && t == 0) {
+    if (publish && t == 0) {
       __hip_atomic_store(A.flags + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     prepared = (r & kPrepared) != 0;
@@ -1468,7 +1475,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
       it = uni(S.nit);
       b = uni(S.nb);
     } else {                               // corrupt block: no ticket was taken
-      if (t == 0) S.nit = A.flow ? ticket() : it + gridDim.x;
+      if (t == 0) S.nit = A.flow ? take_ticket(A) : it + gridDim.x;
       __syncthreads();
       it = uni(S.nit);
       b = it < total ? A.queue[qb + it] : 0u;
@@ -1562,7 +1569,6 @@ int lz_launch_setup(lz_handle* h, hipStream_t s) {
   hipLaunchKernelGGL(k_build_lut, dim3(1), dim3(256), 0, s, v.base, v.off_tables, v.prob_bits[0], h->ws.lut);
   const uint64_t nb = v.n_blocks;
   const uint32_t grid = (uint32_t)std::min<uint64_t>(4096, (nb + 255) / 256 + 1);
-  hipLaunchKernelGGL(k_fill_u32, dim3(grid), dim3(256), 0, s, h->ws.flags, nb, 0u);
   hipLaunchKernelGGL(k_fill_u32, dim3(grid), dim3(256), 0, s, h->ws.mark, nb, 0u);
   hipLaunchKernelGGL(k_fill_u64, dim3(grid), dim3(256), 0, s, h->ws.addr, nb, 0ull);
   // k_closure takes a list entry as pushed once its upper half is the call's
@@ -1584,7 +1590,9 @@ int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
   A.queue = h->ws.queue;
   A.out = out;
   const uint32_t slots = (uint32_t)(h->n_cu * std::max(1u, h->tune.wg_per_cu));
-  if (h->tune.sync_mode == 0) {
+  // one level: nothing to wait for, and tickets are all overhead (32 MiB of
+  // noise, stored blocks: 112 us by ticket, 68 us in static slices)
+  if (h->tune.sync_mode == 0 && h->av.n_levels > 1) {
     A.flow = flow_mode(A, reinterpret_cast<uintptr_t>(out));
     A.q_end = (uint32_t)h->av.n_blocks;
     hipLaunchKernelGGL(k_decode, dim3(std::min(A.q_end, slots)), dim3(kWG), 0, s, A);
@@ -2470,7 +2478,7 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   A.out = d_out;
   const uint32_t slots = (uint32_t)(h->n_cu * std::max(1u, h->tune.wg_per_cu));
   const uint32_t grid = (uint32_t)std::min<uint64_t>(slots, std::max<uint64_t>(1, v.n_blocks));
-  if (h->tune.req_sync_mode == 0) {
+  if (h->tune.req_sync_mode == 0 && v.n_levels > 1) {
     // scratch slots are whole lines; blocks decoded straight into the output lie
     // at d_out - single_off plus a multiple of the block size
     const uint64_t at = reinterpret_cast<uintptr_t>(d_out) - single_off;

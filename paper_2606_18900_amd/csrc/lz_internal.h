@@ -23,6 +23,10 @@ constexpr uint32_t kMaxPSeq = 12;
 constexpr uint32_t kMaxOffsetWidth = 5;   // absolute offsets below 2^40
 constexpr uint32_t kMaxLevels = 64;
 
+// Workspace::flags of a block that no block copies from: nothing waits for it,
+// so its flag is never set
+constexpr uint32_t kFlagLeaf = 0xFFFFFFFFu;
+
 // status bits latched by kernels in the workspace status word
 enum : uint32_t {
   kStCorrupt = 1u,     // payload failed a decode check
@@ -49,7 +53,7 @@ struct Workspace {
   uint32_t* lut;          // 4096 packed literal decode entries
   uint32_t* queue;        // n_blocks: whole-file level-ordered block ids
   uint32_t* level_ptr;    // 65: level offsets into queue
-  uint32_t* flags;        // n_blocks: completion epoch per block
+  uint32_t* flags;        // n_blocks: completion epoch per block, or kFlagLeaf
   uint32_t* mark;         // n_blocks: request epoch per block (closure)
   uint64_t* addr;         // n_blocks: device address of decoded block bytes
   uint32_t* rqueue;       // n_blocks: request closure queue (level order)
