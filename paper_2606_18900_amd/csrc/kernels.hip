@@ -40,7 +40,7 @@ constexpr uint32_t kB = 1u << kMaxBlockLog2;      // largest block: 16 KiB tile
 constexpr uint32_t kMaxSeq = 1025;                // B/m + 1 for B = 16 KiB, m = 16
 constexpr uint32_t kLutLit = 1u << kMaxPLit;      // 4096 packed literal entries
 constexpr uint32_t kL = 1u << 16;                 // rANS state lower bound
-constexpr uint32_t kFastLen = 64;                 // in-block matches copied by one lane
+constexpr uint32_t kFastLen = 256;                // longest in-block match copied in pieces
 constexpr uint32_t kClkSlots = 16;                // stage clocks: 9 stages, block count, events
 constexpr uint32_t kPrepRing = 5120;              // payload prefix kept in the literal rings
 constexpr uint32_t kDeps = 256;                   // dependencies whose ids are kept in LDS
@@ -1150,13 +1150,13 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   // is read and it is final once every earlier match writing into it is done.
   // 4a: per match a (sequence order): destination, length, block-relative
   //     source and period, and the index range of earlier in-block matches
-  //     whose destinations its window meets (two binary searches over the
-  //     sorted, disjoint destinations);
+  //     whose destinations its window meets;
   // 4b: wave 0 copies them in passes over 64-entry chunks (every earlier
   //     chunk complete): a pass takes every pending match whose predecessors
-  //     are done.  Short matches (at most 64 bytes, no overlap with themselves,
-  //     source inside the tile) are copied by their own lane from four-byte
-  //     words; the others by the whole wave, one at a time.
+  //     are done.  Matches of at most 256 bytes with their source inside the
+  //     tile that do not overlap themselves or repeat one byte are copied
+  //     together, in 16-byte pieces; the others by the whole wave, one at a
+  //     time.
   // With at most 64 in-block matches (the common case) stage 2 has written
   // their fields to their own small arrays and only wave 0 works on them: the
   // sequence tables are free, and waves 1..3 prepare the next block
@@ -1239,17 +1239,6 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   if (wv == 0 && cnt) {
     // wave 0's passes bound this stage: it wins issue on its SIMD meanwhile
     __builtin_amdgcn_s_setprio(2);
-    if (small) {                             // fields from stage 2 (before two barriers)
-      if (a0 < a1) {
-        const uint32_t pk = Fp[a0];
-        md0[0] = Fd[a0];
-        mM[0] = Fl[a0];
-        ms[0] = pk & 0xFFFFu;
-        md[0] = pk >> 16;
-      }
-      ranges();
-      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    }
     bool bad = false;
     // whole-wave copy of an in-block match (any length, period and source;
     // uniform arguments): a short repeating one a byte per lane, the rest in
@@ -1279,38 +1268,82 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
       const uint32_t a = c0 + lane;
       const bool have = a < cnt;
       const uint32_t aa = have ? a : c0;
-      const uint32_t rng = Fr[aa];
-      const uint32_t plo = rng & 63u, phi = (rng >> 8) & 63u;
-      const uint64_t needm = have && phi > plo ? (1ull << phi) - (1ull << plo) : 0ull;
-      const uint32_t pk = Fp[aa];
-      const uint32_t dst = Fd[aa], len = Fl[aa];
+      const uint32_t pk = Fp[aa], dst = Fd[aa], len = Fl[aa];
       const int32_t s = (int32_t)(pk & 0xFFFFu) - 16384;
       const uint32_t d = (pk >> 16) & 0x7FFFu;
-      const bool fast = d >= len && len <= kFastLen && s >= 0;
+      uint32_t plo, phi;                      // the earlier matches of the chunk it copies from
+      if (small) {
+        // the matches that end at or before the window's start, and those that
+        // start before its end: both arrays ascend, so eight of the 64 entries
+        // name the group of eight that the bound lies in
+        const uint32_t beg = have ? dst : 0xFFFFu, end = have ? dst + len : 0xFFFFu;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        S.fdst[lane] = (uint16_t)beg;
+        S.frng[lane] = (uint16_t)end;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        auto below = [&](uint32_t mine, const uint16_t* all, uint32_t x) {    // entries below x
+          uint32_t g = 0;
+#pragma unroll
+          for (uint32_t k = 0; k < 8; k++) g += __builtin_amdgcn_readlane(mine, 8 * k + 7) < x ? 1u : 0u;
+          const u32x4 v = ld128(reinterpret_cast<const uint8_t*>(all + 8 * min(g, 7u)));
+          uint32_t n = 8 * min(g, 7u);
+#pragma unroll
+          for (uint32_t k = 0; k < 4; k++) n += ((v[k] & 0xFFFFu) < x ? 1u : 0u) + ((v[k] >> 16) < x ? 1u : 0u);
+          return n;
+        };
+        const int32_t we = s + (int32_t)min(d, len);
+        plo = min(below(end, S.frng, (uint32_t)max(s, 0) + 1), 63u);
+        phi = min(below(beg, S.fdst, (uint32_t)max(we, 0)), 63u);
+      } else {
+        const uint32_t rng = Fr[aa];
+        plo = rng & 63u;
+        phi = (rng >> 8) & 63u;
+      }
+      const uint64_t needm = have && phi > plo ? (1ull << phi) - (1ull << plo) : 0ull;
+      const bool fast = s >= 0 && len <= kFastLen && (d >= len || d == 1);
+      const uint32_t nit = (len + 63) >> 6;   // its 64-byte pieces
       bool pending = have;
       uint64_t done = ~__ballot(pending);
-      for (uint32_t pass = 0; pass <= 64; pass++) {
+      for (uint32_t pass = 0; pass < 128; pass++) {   // at least one match a pass
         const bool ready = pending && (needm & ~done) == 0;
         const uint64_t m = __ballot(ready);
         if (!m) break;
         CLK_ADD(S, 10, 1);
-        const uint64_t mf = __ballot(ready && fast);
+        uint64_t mf = __ballot(ready && fast), later = 0;
         if (mf) {
-          // the ready matches side by side, then sixteen at a time, four lanes
-          // a match, each lane its 16 bytes: a pass has about ten ready matches
-          // of some 20 bytes, so one lane a match (17 words read, up to 64
-          // byte stores) left most lanes idle behind the longest match
-          if (ready && fast) S.rdy[mbcnt(mf)] = (uint64_t)(dst | (len << 16)) | ((uint64_t)(uint32_t)s << 32);
+          // the ready matches' 64-byte pieces side by side, then sixteen at a
+          // time, four lanes a piece, each lane 16 bytes: a pass has about ten
+          // ready matches of some 20 bytes, so one lane a match (17 words read,
+          // up to 64 byte stores) left most lanes idle behind the longest one
+          uint32_t at = mbcnt(mf), n = (uint32_t)__popcll(mf);
+          if (__ballot(ready && fast && nit > 1)) {
+            at = wave_scan(ready && fast ? nit : 0u);
+            later = __ballot(ready && fast && at > 64);        // no room: in the next pass
+            mf &= ~later;
+            n = __builtin_amdgcn_readlane(at, 63 - (uint32_t)__builtin_clzll(mf));
+            at -= nit;
+          }
+          if (ready && fast && at + nit <= 64)
+            for (uint32_t u = 0; u < nit; u++)
+              S.rdy[at + u] = (uint64_t)(dst | (len << 16)) |
+                              ((uint64_t)((uint32_t)s | (u << 22) | (d == 1 ? 1u << 31 : 0u)) << 32);
           __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-          const uint32_t n = (uint32_t)__popcll(mf), sub = 16 * (lane & 3);
+          const uint32_t sub = 16 * (lane & 3);
           for (uint32_t g0 = 0; g0 < n; g0 += 16) {
             const uint32_t i = g0 + (lane >> 2);
             const uint64_t q = S.rdy[min(i, n - 1)];
-            const uint32_t L = (uint32_t)q >> 16;
-            // the last piece of 16 bytes or more is moved back to end with the match
-            const uint32_t k = L >= 16 ? min(sub, L - 16) : 0u;
-            if (i < n && sub < L)
-              st_upto16(S.tile + ((uint32_t)q & 0xFFFFu) + k, ld128(S.tile + (uint32_t)(q >> 32) + k), min(L, 16u));
+            const uint32_t L = (uint32_t)q >> 16, h = (uint32_t)(q >> 32), o = ((h >> 16) & 0xC0u) + sub;
+            if (i < n && o < L) {
+              // the last piece of 16 bytes or more is moved back to end with the match
+              const uint32_t k = L >= 16 ? min(o, L - 16) : 0u;
+              const bool one = h >> 31;       // the byte before the match, repeated
+              u32x4 v = ld128(S.tile + (h & 0xFFFFu) + (one ? 0u : k));
+              if (one) {
+                const uint32_t x = (v[0] & 0xFFu) * 0x01010101u;
+                v = u32x4{x, x, x, x};
+              }
+              st_upto16(S.tile + ((uint32_t)q & 0xFFFFu) + k, v, min(L, 16u));
+            }
           }
         }
         uint64_t slow = __ballot(ready && !fast);
@@ -1324,8 +1357,8 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
                      (int32_t)(k & 0xFFFFu) - 16384, (k >> 16) & 0x7FFFu);
         }
         CLK_ADD(S, 12, CLK_NOW() - c1_);
-        pending = pending && !ready;
-        done |= m;
+        pending = pending && (!ready || ((later >> lane) & 1));
+        done |= m & ~later;
         // the next pass reads what this one wrote (LDS operations of a wave
         // are performed in order; the fence keeps the compiler from moving
         // the reads above the stores)
