@@ -117,6 +117,9 @@ struct Smem {
                                // yet; some block copies from it
   uint32_t err, next, nin;
   uint32_t nit, nb;            // the workgroup's next ticket and block
+  uint32_t nnit;               // the ticket after that, taken while the next block is prepared
+                               // (~0: not taken yet)
+  uint32_t look[16], lookok;   // the next block's directory entry, list bounds and flag
 #ifdef LZ_STAGE_CLOCKS
   uint64_t clk[kClkSlots], clk_last;
 #endif
@@ -691,6 +694,10 @@ __device__ __forceinline__ void put_prep(Smem& S, const BlockDir& d, const Strea
   }
 }
 
+__device__ __forceinline__ uint32_t take_ticket(const DevArgs& A) {
+  return __hip_atomic_fetch_add(A.ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Stages 0 and 1 of block b ("preparing" it): the payload prefix is copied
 // into LDS, the four stream records are parsed and checked, and the CMD, MLEN
 // and OFF streams are decoded into the sequence tables.  The literal record
@@ -725,6 +732,36 @@ __device__ __forceinline__ void put_deps(Smem& S, const DevArgs& A, const Deps& 
     S.used = d.used;
     S.wait = 0;
   }
+}
+
+// What prep needs to know of block b before it can load anything, as one word
+// per lane: its directory entry (lanes 0..7), the bounds of its dependency
+// list (8..11) and its flag (12).
+__device__ __forceinline__ uint32_t look_word(const DevArgs& A, uint32_t b) {
+  const uint32_t lane = lane_id();
+  const uint8_t* p = A.arc + A.off_dir + (uint64_t)b * kDirEntry + 4 * lane;
+  if (lane >= 8) p = A.arc + A.off_dep_ptr + 8ull * b + 4 * (lane - 8);
+  if (lane == 12) p = reinterpret_cast<const uint8_t*>(A.flags + b);
+  return lane < 13 ? ld32(p) : 0u;
+}
+__device__ __forceinline__ BlockDir look_dir(const Smem& S, const DevArgs& A, uint32_t b) {
+  const uint64_t B = 1ull << A.bl, sb = (uint64_t)b << A.bl;
+  BlockDir d;
+  d.poff = (uint64_t)uni(S.look[0]) | ((uint64_t)uni(S.look[1]) << 32);
+  d.plen = uni(S.look[2]);
+  d.ns = uni(S.look[3]);
+  d.nlit = uni(S.look[4]);
+  d.blen = (uint32_t)((sb + B <= A.n) ? B : A.n - sb);
+  return d;
+}
+__device__ __forceinline__ Deps look_deps(const Smem& S, const DevArgs& A) {
+  Deps d = {0, 0, 0};
+  if (A.flow) {
+    d.at = (uint64_t)uni(S.look[8]) | ((uint64_t)uni(S.look[9]) << 32);
+    d.n = uni(S.look[10]) - uni(S.look[8]);
+    d.used = uni(S.look[12]) != kFlagLeaf ? 1u : 0u;
+  }
+  return d;
 }
 
 // prep_tile: all four waves.  The first min(plen, 16 KiB) payload bytes go
@@ -786,10 +823,13 @@ __device__ __forceinline__ void prep_tile(Smem& S, const DevArgs& A, uint32_t b)
 // the rings are not in use.
 __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b) {
   const uint32_t wv = uni(threadIdx.x >> 6), lane = lane_id();
-  const BlockDir d = block_dir(A, b);
-  const Deps dp = block_deps(A, b);
+  const bool looked = uni(S.lookok) != 0;
+  const BlockDir d = looked ? look_dir(S, A, b) : block_dir(A, b);
+  const Deps dp = looked ? look_deps(S, A) : block_deps(A, b);
   const uint8_t* pay = A.arc + A.off_payload + d.poff;
   const uint32_t hlen = min(d.plen, kPrepRing);
+  uint32_t nn = 0;
+  if (A.flow && threadIdx.x == 64) nn = take_ticket(A);    // for the block after this one
   {
     const uint32_t n16 = hlen >> 4;
     const bool tail = lane < (hlen & 15u);           // bytes past the last 16
@@ -824,6 +864,7 @@ __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b)
     S.pok = ok ? 1u : 0u;
     put_prep(S, d, sl, S.prep, ok);
     S.next = 0;
+    S.nnit = nn;
   }
 }
 
@@ -880,12 +921,8 @@ __device__ __forceinline__ void copy_long(Smem& S, const DevArgs& A, uint64_t sb
 // a finished block's flag.  The next place and block go to S.nit and S.nb
 // (kNext of the result; unset after corrupt data); kPrepared: that block has
 // been prepared meanwhile, by waves 1..3 while wave 0 resolved b's in-block
-// matches; kUsed: other blocks may be waiting for this one.  Every loop below is bounded by values read from global memory
+// matches; kUsed: this block is still to be published.  Every loop below is bounded by values read from global memory
 // (directory, stream headers) or by the spin limit.
-__device__ __forceinline__ uint32_t take_ticket(const DevArgs& A) {
-  return __hip_atomic_fetch_add(A.ctl + kCtlTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 constexpr uint32_t kPrepared = 1, kNext = 2, kUsed = 4;
 __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint32_t b, uint32_t qb,
                                                  uint32_t total, uint32_t it, uint32_t epoch) {
@@ -899,6 +936,14 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   const uint32_t nd = A.flow ? uni(S.ndep) : 0u;
   const uint32_t dep = t < min(nd, kDeps) ? S.dep[t] : 0u;
   const bool used = A.flow && uni(S.used);
+  // The workgroup's next place: known when the ticket was taken while b was
+  // prepared, or from the slice.  Wave 1 then reads the block's id during
+  // stage 2, what prep_ring needs of it during the literal decode, and touches
+  // the block's payload after it, so that none of prep_ring's and the next
+  // literal decode's loads waits for HBM.
+  const uint32_t known = A.flow ? uni(S.nnit) : it + gridDim.x;
+  uint32_t nbq = ~0u;
+  if (wv == 1 && known < total) nbq = A.queue[qb + known];
   uint32_t flag = epoch;
   if (t < min(nd, kDeps)) flag = __hip_atomic_load(A.flags + dep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t poff = (uint64_t)uni(S.pdir[0]) | ((uint64_t)uni(S.pdir[1]) << 32);
@@ -1038,9 +1083,11 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     first.v = first.w = u32x4{};
     first.M = first.d0 = 0;
     if (!wait) ext_load(slot, first);
-    // the workgroup's next ticket; the literal decode hides the round trip
-    uint32_t nit = 0, nbq = ~0u;
-    if (t == 64) nit = A.flow ? take_ticket(A) : it + gridDim.x;
+    // a first block's next ticket; the literal decode hides the round trip
+    uint32_t nit = known, look = 0;
+    nbq = uni(nbq);
+    if (nbq != ~0u) look = look_word(A, nbq);
+    if (t == 64 && known == ~0u) nit = take_ticket(A);
     if (wv < Glit) {
       const uint32_t g = wv;
       bool okg;
@@ -1066,7 +1113,14 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
       }
     }
     CLK_MARK(S, 4);
-    if (t == 64 && nit < total) nbq = A.queue[qb + nit];
+    uint32_t touch = 0;
+    if (nbq != ~0u) {                       // wave 1: the payload into this XCD's L2
+      if (lane < 16) S.look[lane] = look;
+      const uint64_t po = (uint64_t)__builtin_amdgcn_readlane(look, 0) |
+                          ((uint64_t)__builtin_amdgcn_readlane(look, 1) << 32);
+      if (128 * lane < __builtin_amdgcn_readlane(look, 2)) touch = A.arc[A.off_payload + po + 128 * lane];
+    }
+    if (t == 64 && known == ~0u && nit < total) nbq = A.queue[qb + nit];
     if (wait) {
       // The blocks b copies from have smaller tickets, so their workgroups
       // run or have finished, and none of them waits for this one.
@@ -1134,7 +1188,10 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     if (t == 64) {
       S.nit = nit;
       S.nb = nbq;
+      S.lookok = known != ~0u ? 1u : 0u;
+      S.nnit = ~0u;
     }
+    if (nbq != ~0u) S.look[15] = touch;     // not read: keeps the loads
   }
   __syncthreads();
   if (S.err) {
@@ -1232,6 +1289,24 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     __syncthreads();
   }
   CLK_MARK(S, 6);
+  // ---- stage 5: tile -> HBM by n threads, this one the i-th; through the L2,
+  // to where every XCD sees it, if some block copies from this one
+  auto store_tile = [&](uint32_t i, uint32_t n) {
+    if (!dst) return;
+    if (used) {
+      uint64_t* d8 = reinterpret_cast<uint64_t*>(dst);
+      const uint64_t* s8 = reinterpret_cast<const uint64_t*>(S.tile);
+      for (uint32_t c = i; c < blen >> 3; c += n)
+        __hip_atomic_store(d8 + c, s8[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (uint32_t c = (blen & ~7u) + i; c < blen; c += n)
+        __hip_atomic_store(dst + c, S.tile[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      const uint4* s4 = reinterpret_cast<const uint4*>(S.tile);
+      uint4* d4 = reinterpret_cast<uint4*>(dst);
+      for (uint32_t c = i; c < blen >> 4; c += n) d4[c] = s4[c];
+      for (uint32_t c = (blen & ~15u) + i; c < blen; c += n) dst[c] = S.tile[c];
+    }
+  };
   // No workgroup barrier from here to the end of the passes: wave 0 and
   // waves 1..3 run different code.
   const bool ov = small && nb != ~0u;
@@ -1369,6 +1444,14 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     if (bad) S.err = 1;
     __builtin_amdgcn_s_setprio(1);
     CLK_ADD(S, 13, CLK_NOW() - c4_);
+  }
+  if (wv == 0 && ov) {
+    // stage 5 by wave 0 alone, while the others prepare the next block
+    store_tile(lane, 64);
+    if (used) {
+      vm_wait();
+      if (lane == 0) __hip_atomic_store(A.flags + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   } else if (wv != 0 && ov) {
     // the preparation has slack (it ends well before wave 0's passes): it
     // yields issue to the waves on their workgroups' critical paths
@@ -1386,28 +1469,13 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     return kNext | kUsed | (prepared ? kPrepared : 0u);
   }
 
-  // ---- stage 5: tile -> HBM with 16-byte stores
-  if (dst) {
-    const uint32_t full = blen >> 4;
-    const uint4* s4 = reinterpret_cast<const uint4*>(S.tile);
-    uint4* d4 = reinterpret_cast<uint4*>(dst);
-    if (used) {                // through the L2, to where every XCD sees it
-      uint64_t* d8 = reinterpret_cast<uint64_t*>(dst);
-      const uint64_t* s8 = reinterpret_cast<const uint64_t*>(S.tile);
-      for (uint32_t c = t; c < blen >> 3; c += kWG)
-        __hip_atomic_store(d8 + c, s8[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (uint32_t c = (blen & ~7u) + t; c < blen; c += kWG)
-        __hip_atomic_store(dst + c, S.tile[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      for (uint32_t c = t; c < full; c += kWG) d4[c] = s4[c];
-      for (uint32_t c = (full << 4) + t; c < blen; c += kWG) dst[c] = S.tile[c];
-    }
-  }
+  // ---- stage 5, unless wave 0 has done it
+  if (!ov) store_tile(t, kWG);
   CLK_MARK(S, 8);
 #ifdef LZ_STAGE_CLOCKS
   if (t == 0) S.clk[9] += 1;
 #endif
-  return kNext | (prepared ? kPrepared : 0u) | (used ? kUsed : 0u);
+  return kNext | (prepared ? kPrepared : 0u) | (used && !ov ? kUsed : 0u);
 }
 
 
@@ -1484,7 +1552,10 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
   }
   const uint32_t total = qe - qb;
   if (blockIdx.x >= total) return;         // more workgroups than blocks
-  if (A.flow && t == 0) S.nit = take_ticket(A);
+  if (A.flow && t == 0) {
+    S.nit = take_ticket(A);
+    S.nnit = ~0u;
+  }
 #ifdef LZ_STAGE_CLOCKS
   if (t < kClkSlots) S.clk[t] = 0;
 #endif
@@ -1508,7 +1579,10 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
       it = uni(S.nit);
       b = uni(S.nb);
     } else {                               // corrupt block: no ticket was taken
-      if (t == 0) S.nit = A.flow ? take_ticket(A) : it + gridDim.x;
+      if (t == 0) {
+        S.nit = !A.flow ? it + gridDim.x : (S.nnit != ~0u ? S.nnit : take_ticket(A));
+        S.nnit = ~0u;
+      }
       __syncthreads();
       it = uni(S.nit);
       b = it < total ? A.queue[qb + it] : 0u;
