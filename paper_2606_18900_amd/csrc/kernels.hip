@@ -43,6 +43,7 @@ constexpr uint32_t kL = 1u << 16;                 // rANS state lower bound
 constexpr uint32_t kFastLen = 256;                // longest in-block match copied in pieces
 constexpr uint32_t kClkSlots = 16;                // stage clocks: 9 stages, block count, events
 constexpr uint32_t kPrepRing = 5120;              // payload prefix kept in the literal rings
+constexpr uint32_t kBuckets = 128;                // a short stream's slots in so many buckets
 constexpr uint32_t kDeps = 256;                   // dependencies whose ids are kept in LDS
 
 // Stage clocks (instrumented build only, -DLZ_STAGE_CLOCKS): a barrier, then
@@ -78,8 +79,11 @@ struct Smem {
   uint32_t lut[kLutLit];       // literal decode entries: symbol | f << 8 | (slot - c) << 20
   alignas(16) uint8_t tile[kB + 16];   // output tile (16-byte reads may start at its last
                                // byte); until stage 3 a copy of the payload prefix
-  uint16_t cum[3][257];        // CMD, MLEN, OFF cumulative frequencies
-  uint8_t bkt[3][256];         // per stream: symbol owning the first slot of each bucket
+  // CMD, MLEN, OFF: the symbols that occur, in order (the k-th one: its first
+  // slot and its value), and which of them owns the first slot of each bucket
+  uint16_t cum[3][257];
+  uint8_t sym[3][256];
+  uint8_t bkt[3][kBuckets];
   uint16_t lit[kMaxSeq + 1];   // LL, then literal start of each sequence ([ns] = n_lit);
                                // stage 4: destination of in-block match a
   uint16_t out[kMaxSeq + 1];   // ML, then output start of each sequence ([ns] = block length);
@@ -117,9 +121,6 @@ struct Smem {
                                // yet; some block copies from it
   uint32_t err, next, nin;
   uint32_t nit, nb;            // the workgroup's next ticket and block
-  uint32_t nnit;               // the ticket after that, taken while the next block is prepared
-                               // (~0: not taken yet)
-  uint32_t look[16], lookok;   // the next block's directory entry, list bounds and flag
 #ifdef LZ_STAGE_CLOCKS
   uint64_t clk[kClkSlots], clk_last;
 #endif
@@ -227,54 +228,81 @@ struct Stream {
 // Parse and check the record at *off (16-byte aligned) of the LDS copy `hp` of
 // the first hlen payload bytes; records end within plen.  With `staged` the
 // whole record must lie in the copy (the short streams are decoded from it).
+// No early return and the group word counts apart (counts_ok): the four
+// records' headers are a chain of LDS reads as it is.
 __device__ __forceinline__ bool parse_stream(const uint8_t* hp, uint32_t hlen, uint32_t plen,
                                              uint32_t* off, uint32_t want, uint32_t maxK,
                                              bool staged, Stream& s) {
-  if (*off + 16 > hlen) return false;
-  const uint4 h = *reinterpret_cast<const uint4*>(hp + *off);
-  s.mode = uni(h.x & 0xFFu);
-  s.csym = uni((h.x >> 8) & 0xFFu);
-  s.K = uni(h.x >> 16);
-  s.n = uni(h.y);
-  s.nw = uni(h.z);
-  s.blen = uni(h.w);
+  bool ok = *off + 16 <= hlen;
+  const u32x4 h = *reinterpret_cast<const u32x4*>(hp + (ok ? *off : 0u));
+  const uint32_t hx = uni(h[0]);
+  s.mode = hx & 0xFFu;
+  s.csym = (hx >> 8) & 0xFFu;
+  s.K = hx >> 16;
+  s.n = uni(h[1]);
+  s.nw = uni(h[2]);
+  s.blen = uni(h[3]);
   s.body = *off + 16;
-  if (s.n != want) return false;
-  if (staged && (uint64_t)s.body + s.blen > hlen) return false;
+  const uint64_t end = (uint64_t)s.body + s.blen;
+  ok = ok && s.n == want && !(staged && end > hlen);
+  const uint32_t G = (s.K + 63) >> 6;
+  bool fits;
   switch (s.mode) {
-    case kModeEmpty: if (s.n || s.blen) return false; break;
-    case kModeConst: if (!s.n || s.blen) return false; break;
-    case kModeRaw: if (s.blen != s.n || s.body + s.blen > plen) return false; break;
-    case kModeRans: {
-      const uint32_t G = (s.K + 63) >> 6;
-      if (s.K < 1 || s.K > maxK || !s.n || s.body + s.blen > plen) return false;
-      if ((uint64_t)s.blen != 4ull * s.K + 4ull * G + 2ull * s.nw) return false;
-      if ((uint64_t)s.body + 4ull * s.K + 4ull * G > hlen) return false;
-      const uint32_t* cnt = reinterpret_cast<const uint32_t*>(hp + s.body + 4 * s.K);
-      uint64_t sum = 0;
-      for (uint32_t g = 0; g < G; g++) sum += uni(cnt[g]);
-      if (sum != s.nw) return false;
+    case kModeEmpty: fits = !s.n && !s.blen; break;
+    case kModeConst: fits = s.n && !s.blen; break;
+    case kModeRaw: fits = s.blen == s.n && end <= plen; break;
+    case kModeRans:
+      fits = s.K >= 1 && s.K <= maxK && s.n && end <= plen &&
+             (uint64_t)s.blen == 4ull * s.K + 4ull * G + 2ull * s.nw &&
+             (uint64_t)s.body + 4ull * s.K + 4ull * G <= hlen;
       break;
-    }
-    default: return false;
+    default: fits = false;
   }
-  *off = s.body + ((s.blen + 15u) & ~15u);
-  return true;
+  ok = ok && fits;
+  if (ok) *off = s.body + ((s.blen + 15u) & ~15u);
+  return ok;
 }
 
-// Symbol owning slot u of a short stream, packed like a literal LUT entry.
-// The bucket of u (2^bs slots) names the owner of its first slot; the owner
-// of u is that symbol or one of the at most 2^bs - 1 symbols after it.
-__device__ __forceinline__ uint32_t bucket_sym(const uint16_t* cum, const uint8_t* bkt,
-                                               uint32_t bs, uint32_t u) {
+// The word counts of a record's groups (at most four) add up.  The counts lie
+// in the copy (parse_stream); a read of sixteen bytes from there may run past
+// it, but not past the LDS it lies in.
+__device__ __forceinline__ bool counts_ok(const uint8_t* hp, const Stream& s) {
+  const bool rans = s.mode == kModeRans;
+  const uint32_t G = (s.K + 63) >> 6;
+  const u32x4 c = ld128(hp + (rans ? s.body + 4 * s.K : 0u));
+  uint64_t sum = 0;
+#pragma unroll
+  for (uint32_t g = 0; g < kWaves; g++) sum += g < G ? c[g] : 0u;
+  return !rans | (uni(sum == s.nw) != 0);
+}
+
+// The owner of slot u of a short stream (an index of sym[]), its first slot
+// and its number of slots.  The bucket of u (2^bs slots) names the owner of
+// its first slot; the owner of u is that or one of the next symbols that
+// occur, whose first slots one read brings, so that a symbol takes two LDS
+// round trips, hardly ever more.  (Over all symbols, those that never occur
+// had to be stepped over one read each: 5.6 k cycles for a FASTQ block's CMD
+// stream against 1.7 k for its OFF stream, twice as long.)
+struct Slot {
+  uint32_t k, c0, f;
+};
+__device__ __forceinline__ Slot bucket_sym(const uint16_t* cum, const uint8_t* bkt, uint32_t bs, uint32_t u) {
   uint32_t s = bkt[u >> bs];
-  uint32_t c0 = cum[s], c1 = cum[s + 1];
+  const u32x4 v = ld128(reinterpret_cast<const uint8_t*>(cum + s));     // cum[s .. s + 7]
+  uint32_t c0 = v[0] & 0xFFFFu, c1 = v[0] >> 16;
+#pragma unroll
+  for (uint32_t k = 2; k < 8; k++) {
+    const bool on = c1 <= u;              // false from the owner on: cum[256] is above every slot
+    c0 = on ? c1 : c0;
+    s += on ? 1u : 0u;
+    c1 = on ? (k & 1 ? v[k / 2] >> 16 : v[k / 2] & 0xFFFFu) : c1;
+  }
   while (c1 <= u && s < 255) {
     s++;
     c0 = c1;
     c1 = cum[s + 1];
   }
-  return s | (((c1 - c0) & 0xFFFu) << 8) | ((u - c0) << 20);
+  return Slot{min(s, 255u), c0, c1 - c0};
 }
 
 // Decode a short rANS stream (one group of K <= 64 lanes) with one wave.  The
@@ -287,7 +315,7 @@ __device__ __forceinline__ uint32_t bucket_sym(const uint16_t* cum, const uint8_
 // every word of the group was read.
 template <class Put>
 __device__ bool short_rans(const uint8_t* body, const Stream& s, uint32_t P, const uint16_t* cum,
-                           const uint8_t* bkt, uint32_t bs, Put& put) {
+                           const uint8_t* sym, const uint8_t* bkt, uint32_t bs, Put& put) {
   const uint32_t lane = lane_id();
   const uint32_t K = s.K, n = s.n;
   const bool lane_ok = lane < K;
@@ -302,9 +330,10 @@ __device__ bool short_rans(const uint8_t* body, const Stream& s, uint32_t P, con
   uint32_t pos = 0;
   auto round = [&](bool act) {
     if (act) {
-      const uint32_t en = bucket_sym(cum, bkt, bs, x & mask);
-      x = __umul24((en >> 8) & 0xFFFu, x >> P) + (en >> 20);
-      put(en & 0xFFu);
+      const uint32_t u = x & mask;
+      const Slot o = bucket_sym(cum, bkt, bs, u);
+      x = __umul24(o.f, x >> P) + (u - o.c0);
+      put(sym[o.k]);
     }
     const bool need = act && x < kL;
     const uint64_t bal = __ballot(need);
@@ -634,11 +663,13 @@ __device__ __forceinline__ bool parse_records(const DevArgs& A, const BlockDir& 
                                               Stream& sl) {
   uint32_t off = 0;
   bool ok = d.ns >= 1 && d.ns <= kMaxSeq && d.nlit <= d.blen && (d.poff & 15) == 0;
-  ok = ok && parse_stream(hp, hlen, d.plen, &off, 2 * d.ns, A.seq_lanes, true, sc);
-  ok = ok && parse_stream(hp, hlen, d.plen, &off, 2 * d.ns, A.seq_lanes, true, sm);
-  ok = ok && parse_stream(hp, hlen, d.plen, &off, A.w * d.ns, A.seq_lanes, true, so);
-  ok = ok && parse_stream(hp, hlen, d.plen, &off, d.nlit, A.lit_lanes, false, sl);
-  return ok;
+  ok &= parse_stream(hp, hlen, d.plen, &off, 2 * d.ns, A.seq_lanes, true, sc);
+  ok &= parse_stream(hp, hlen, d.plen, &off, 2 * d.ns, A.seq_lanes, true, sm);
+  ok &= parse_stream(hp, hlen, d.plen, &off, A.w * d.ns, A.seq_lanes, true, so);
+  ok &= parse_stream(hp, hlen, d.plen, &off, d.nlit, A.lit_lanes, false, sl);
+  if (!ok) return false;
+  const bool c0 = counts_ok(hp, sc), c1 = counts_ok(hp, sm), c2 = counts_ok(hp, so), c3 = counts_ok(hp, sl);
+  return c0 & c1 & c2 & c3;
 }
 
 // Short stream `role` of a block with ns sequences, by one wave: 0 CMD ->
@@ -661,9 +692,8 @@ __device__ bool short_stream(Smem& S, const DevArgs& A, uint32_t role, const Str
     __builtin_amdgcn_wave_barrier();
   }
   if (s.mode == kModeRans) {
-    const uint32_t P = A.P[1 + role];
-    const uint32_t bs = P > 8 ? P - 8 : 0u;
-    return short_rans(hp + s.body, s, P, S.cum[role], S.bkt[role], bs, put);
+    const uint32_t P = A.P[1 + role];                 // at least 8
+    return short_rans(hp + s.body, s, P, S.cum[role], S.sym[role], S.bkt[role], P - 7, put);
   }
   if (s.mode == kModeRaw || s.mode == kModeConst) {
     const uint8_t* src = hp + s.body;
@@ -734,36 +764,6 @@ __device__ __forceinline__ void put_deps(Smem& S, const DevArgs& A, const Deps& 
   }
 }
 
-// What prep needs to know of block b before it can load anything, as one word
-// per lane: its directory entry (lanes 0..7), the bounds of its dependency
-// list (8..11) and its flag (12).
-__device__ __forceinline__ uint32_t look_word(const DevArgs& A, uint32_t b) {
-  const uint32_t lane = lane_id();
-  const uint8_t* p = A.arc + A.off_dir + (uint64_t)b * kDirEntry + 4 * lane;
-  if (lane >= 8) p = A.arc + A.off_dep_ptr + 8ull * b + 4 * (lane - 8);
-  if (lane == 12) p = reinterpret_cast<const uint8_t*>(A.flags + b);
-  return lane < 13 ? ld32(p) : 0u;
-}
-__device__ __forceinline__ BlockDir look_dir(const Smem& S, const DevArgs& A, uint32_t b) {
-  const uint64_t B = 1ull << A.bl, sb = (uint64_t)b << A.bl;
-  BlockDir d;
-  d.poff = (uint64_t)uni(S.look[0]) | ((uint64_t)uni(S.look[1]) << 32);
-  d.plen = uni(S.look[2]);
-  d.ns = uni(S.look[3]);
-  d.nlit = uni(S.look[4]);
-  d.blen = (uint32_t)((sb + B <= A.n) ? B : A.n - sb);
-  return d;
-}
-__device__ __forceinline__ Deps look_deps(const Smem& S, const DevArgs& A) {
-  Deps d = {0, 0, 0};
-  if (A.flow) {
-    d.at = (uint64_t)uni(S.look[8]) | ((uint64_t)uni(S.look[9]) << 32);
-    d.n = uni(S.look[10]) - uni(S.look[8]);
-    d.used = uni(S.look[12]) != kFlagLeaf ? 1u : 0u;
-  }
-  return d;
-}
-
 // prep_tile: all four waves.  The first min(plen, 16 KiB) payload bytes go
 // into the tile (free until the literal stage) with one round of 16-byte
 // loads; waves 0..2 decode the short streams from there (at most about 9.3 KB
@@ -823,13 +823,10 @@ __device__ __forceinline__ void prep_tile(Smem& S, const DevArgs& A, uint32_t b)
 // the rings are not in use.
 __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b) {
   const uint32_t wv = uni(threadIdx.x >> 6), lane = lane_id();
-  const bool looked = uni(S.lookok) != 0;
-  const BlockDir d = looked ? look_dir(S, A, b) : block_dir(A, b);
-  const Deps dp = looked ? look_deps(S, A) : block_deps(A, b);
+  const BlockDir d = block_dir(A, b);
+  const Deps dp = block_deps(A, b);
   const uint8_t* pay = A.arc + A.off_payload + d.poff;
   const uint32_t hlen = min(d.plen, kPrepRing);
-  uint32_t nn = 0;
-  if (A.flow && threadIdx.x == 64) nn = take_ticket(A);    // for the block after this one
   {
     const uint32_t n16 = hlen >> 4;
     const bool tail = lane < (hlen & 15u);           // bytes past the last 16
@@ -864,7 +861,6 @@ __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b)
     S.pok = ok ? 1u : 0u;
     put_prep(S, d, sl, S.prep, ok);
     S.next = 0;
-    S.nnit = nn;
   }
 }
 
@@ -936,14 +932,6 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   const uint32_t nd = A.flow ? uni(S.ndep) : 0u;
   const uint32_t dep = t < min(nd, kDeps) ? S.dep[t] : 0u;
   const bool used = A.flow && uni(S.used);
-  // The workgroup's next place: known when the ticket was taken while b was
-  // prepared, or from the slice.  Wave 1 then reads the block's id during
-  // stage 2, what prep_ring needs of it during the literal decode, and touches
-  // the block's payload after it, so that none of prep_ring's and the next
-  // literal decode's loads waits for HBM.
-  const uint32_t known = A.flow ? uni(S.nnit) : it + gridDim.x;
-  uint32_t nbq = ~0u;
-  if (wv == 1 && known < total) nbq = A.queue[qb + known];
   uint32_t flag = epoch;
   if (t < min(nd, kDeps)) flag = __hip_atomic_load(A.flags + dep, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint64_t poff = (uint64_t)uni(S.pdir[0]) | ((uint64_t)uni(S.pdir[1]) << 32);
@@ -968,22 +956,17 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   if (!one || wv == 0) {
     const uint32_t per = (ns + kWG - 1) / kWG;   // <= 5
     const uint32_t j0 = min(ns, t * per), j1 = min(ns, j0 + per);
-    uint32_t ll[5], ml[5];
     uint32_t v[3] = {0, 0, 0};
     bool bad = false;
-#pragma unroll
-    for (uint32_t q = 0; q < 5; q++) {
-      const uint32_t j = j0 + q;
-      ll[q] = j < j1 ? S.lit[j] : 0u;
-      ml[q] = j < j1 ? S.out[j] : 0u;
-      uint32_t inb = 0;
-      if (j < j1 && ml[q]) {
-        const uint64_t of = (uint64_t)S.oflo[j] | ((uint64_t)S.ofhi[j] << 32);
-        inb = of + ml[q] > sb ? 1u : 0u;
-      }
-      v[0] += ll[q];
-      v[1] += ll[q] + ml[q];
-      v[2] += inb;
+    // one sequence per thread up to 256 of them (loops not unrolled: for their
+    // most of five iterations a thread, all the others paid)
+#pragma unroll 1
+    for (uint32_t j = j0; j < j1; j++) {
+      const uint32_t ll = S.lit[j], ml = S.out[j];
+      const uint64_t of = (uint64_t)S.oflo[j] | ((uint64_t)S.ofhi[j] << 32);
+      v[0] += ll;
+      v[1] += ll + ml;
+      v[2] += ml && of + ml > sb ? 1u : 0u;
     }
     uint32_t pre[3], tot[3];
     if (one) {
@@ -1000,35 +983,33 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     bad |= tl != nlit || to != blen;
     uint32_t pl = pre[0], po = pre[1];
     uint32_t pin = pre[2];
-#pragma unroll
-    for (uint32_t q = 0; q < 5; q++) {
-      const uint32_t j = j0 + q;
-      if (j < j1) {
-        S.lit[j] = (uint16_t)pl;
-        S.out[j] = (uint16_t)po;
-        const uint64_t of = (uint64_t)S.oflo[j] | ((uint64_t)S.ofhi[j] << 32);
-        if (ml[q] == 0) {
-          bad |= (j != ns - 1) || of != 0;
+#pragma unroll 1
+    for (uint32_t j = j0; j < j1; j++) {
+      const uint32_t ll = S.lit[j], ml = S.out[j];
+      const uint64_t of = (uint64_t)S.oflo[j] | ((uint64_t)S.ofhi[j] << 32);
+      S.lit[j] = (uint16_t)pl;
+      S.out[j] = (uint16_t)po;
+      if (ml == 0) {
+        bad |= (j != ns - 1) || of != 0;
+      } else {
+        bad |= ml < A.m || of >= sb + po + ll;
+        if (of + ml <= sb) {
+          S.lst[atomicAdd(&S.next, 1u)] = (uint16_t)j;   // from earlier blocks, any order
         } else {
-          bad |= ml[q] < A.m || of >= sb + po + ll[q];
-          if (of + ml[q] <= sb) {
-            S.lst[atomicAdd(&S.next, 1u)] = (uint16_t)j;   // from earlier blocks, any order
-          } else {
-            S.lst[kMaxSeq - 1 - pin] = (uint16_t)j;        // in-block, in sequence order
-            if (pin < 64) {                                // the common case: its fields at once
-              const uint32_t d0 = po + ll[q];
-              const uint64_t dabs = sb + d0;
-              S.fdst[pin] = (uint16_t)d0;
-              S.flen[pin] = (uint16_t)min(ml[q], blen);
-              S.fpk[pin] = ((uint32_t)((int64_t)of - (int64_t)sb + 16384) & 0xFFFFu) |
-                           ((dabs > of ? (uint32_t)min<uint64_t>(dabs - of, 32767) : 1u) << 16);
-            }
-            pin++;
+          S.lst[kMaxSeq - 1 - pin] = (uint16_t)j;        // in-block, in sequence order
+          if (pin < 64) {                                // the common case: its fields at once
+            const uint32_t d0 = po + ll;
+            const uint64_t dabs = sb + d0;
+            S.fdst[pin] = (uint16_t)d0;
+            S.flen[pin] = (uint16_t)min(ml, blen);
+            S.fpk[pin] = ((uint32_t)((int64_t)of - (int64_t)sb + 16384) & 0xFFFFu) |
+                         ((dabs > of ? (uint32_t)min<uint64_t>(dabs - of, 32767) : 1u) << 16);
           }
+          pin++;
         }
-        pl += ll[q];
-        po += ll[q] + ml[q];
       }
+      pl += ll;
+      po += ll + ml;
     }
     if (t == 0) {
       S.lit[ns] = (uint16_t)min(tl, 65535u);
@@ -1083,11 +1064,11 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     first.v = first.w = u32x4{};
     first.M = first.d0 = 0;
     if (!wait) ext_load(slot, first);
-    // a first block's next ticket; the literal decode hides the round trip
-    uint32_t nit = known, look = 0;
-    nbq = uni(nbq);
-    if (nbq != ~0u) look = look_word(A, nbq);
-    if (t == 64 && known == ~0u) nit = take_ticket(A);
+    // the workgroup's next place; the literal decode hides the ticket's round
+    // trip (several microseconds while every workgroup takes them; taken
+    // during the preparation, one block further ahead, it held that up)
+    uint32_t nit = it + gridDim.x, nbq = ~0u;
+    if (A.flow && t == 64) nit = take_ticket(A);
     if (wv < Glit) {
       const uint32_t g = wv;
       bool okg;
@@ -1113,14 +1094,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
       }
     }
     CLK_MARK(S, 4);
-    uint32_t touch = 0;
-    if (nbq != ~0u) {                       // wave 1: the payload into this XCD's L2
-      if (lane < 16) S.look[lane] = look;
-      const uint64_t po = (uint64_t)__builtin_amdgcn_readlane(look, 0) |
-                          ((uint64_t)__builtin_amdgcn_readlane(look, 1) << 32);
-      if (128 * lane < __builtin_amdgcn_readlane(look, 2)) touch = A.arc[A.off_payload + po + 128 * lane];
-    }
-    if (t == 64 && known == ~0u && nit < total) nbq = A.queue[qb + nit];
+    if (t == 64 && nit < total) nbq = A.queue[qb + nit];
     if (wait) {
       // The blocks b copies from have smaller tickets, so their workgroups
       // run or have finished, and none of them waits for this one.
@@ -1188,10 +1162,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     if (t == 64) {
       S.nit = nit;
       S.nb = nbq;
-      S.lookok = known != ~0u ? 1u : 0u;
-      S.nnit = ~0u;
     }
-    if (nbq != ~0u) S.look[15] = touch;     // not read: keeps the loads
   }
   __syncthreads();
   if (S.err) {
@@ -1490,30 +1461,31 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
   if (t < 3 * 64) {          // waves 0..2: one table each, 4 symbols per lane
     const uint32_t k = t >> 6, lane = t & 63;
     const uint8_t* tab = A.arc + A.off_tables + 512 * (k + 1);
-    uint32_t f[4], sum = 0;
+    uint32_t f[4], sum = 0;                          // slots, and symbols that occur << 16
     for (int q = 0; q < 4; q++) {
       f[q] = (uint32_t)tab[2 * (4 * lane + q)] | ((uint32_t)tab[2 * (4 * lane + q) + 1] << 8);
-      sum += f[q];
+      sum += f[q] + (f[q] ? 1u << 16 : 0u);
     }
-    uint32_t incl = sum;
-    for (int d = 1; d < 64; d <<= 1) {
-      uint32_t y = __shfl_up(incl, d, 64);
-      if (lane >= (uint32_t)d) incl += y;
-    }
+    const uint32_t incl = wave_scan(sum), all = __builtin_amdgcn_readlane(incl, 63);
     uint32_t c = incl - sum;
     for (int q = 0; q < 4; q++) {
-      S.cum[k][4 * lane + q] = (uint16_t)c;
-      c += f[q];
+      if (f[q]) {
+        S.cum[k][c >> 16] = (uint16_t)c;
+        S.sym[k][c >> 16] = (uint8_t)(4 * lane + q);
+      }
+      c += f[q] + (f[q] ? 1u << 16 : 0u);
     }
-    if (lane == 63) S.cum[k][256] = (uint16_t)min(c, 65535u);
+    for (uint32_t r = (all >> 16) + lane; r < 257; r += 64) {     // above every slot
+      S.cum[k][r] = (uint16_t)all;
+      if (r < 256) S.sym[k][r] = 0;
+    }
   }
   vm_wait();                      // this wave's LUT rows, before the barrier
   __syncthreads();
   // bucket index of each short stream: bucket b starts at slot b << bs
-  for (uint32_t e = t; e < 3 * 256; e += kWG) {
-    const uint32_t k = e >> 8, b = e & 255, P = A.P[1 + k];
-    const uint32_t bs = P > 8 ? P - 8 : 0u;
-    if ((b << bs) < (1u << P)) S.bkt[k][b] = (uint8_t)search_sym(S.cum[k], b << bs);
+  for (uint32_t e = t; e < 3 * kBuckets; e += kWG) {
+    const uint32_t k = e / kBuckets, b = e % kBuckets;
+    S.bkt[k][b] = (uint8_t)search_sym(S.cum[k], b << (A.P[1 + k] - 7));
   }
 }
 
@@ -1552,10 +1524,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
   }
   const uint32_t total = qe - qb;
   if (blockIdx.x >= total) return;         // more workgroups than blocks
-  if (A.flow && t == 0) {
-    S.nit = take_ticket(A);
-    S.nnit = ~0u;
-  }
+  if (A.flow && t == 0) S.nit = take_ticket(A);
 #ifdef LZ_STAGE_CLOCKS
   if (t < kClkSlots) S.clk[t] = 0;
 #endif
@@ -1579,10 +1548,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
       it = uni(S.nit);
       b = uni(S.nb);
     } else {                               // corrupt block: no ticket was taken
-      if (t == 0) {
-        S.nit = !A.flow ? it + gridDim.x : (S.nnit != ~0u ? S.nnit : take_ticket(A));
-        S.nnit = ~0u;
-      }
+      if (t == 0) S.nit = A.flow ? take_ticket(A) : it + gridDim.x;
       __syncthreads();
       it = uni(S.nit);
       b = it < total ? A.queue[qb + it] : 0u;
