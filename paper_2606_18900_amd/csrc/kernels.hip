@@ -1934,7 +1934,7 @@ namespace {
 struct ReqArgs {
   const uint8_t* arc;
   uint64_t n, n_blocks, off_dir, off_dep_ptr, off_dep_idx, off_ridx, n_reads;
-  uint32_t bl, mode, direct;
+  uint32_t bl, mode, direct, lmark;
   uint64_t a0, b0;            // mode 0: the single range
   const int64_t* ids;         // mode 1: read ids
   const lz_request* reqs;     // mode 2: requests
@@ -2164,12 +2164,17 @@ __device__ __forceinline__ uint32_t block_level(const ReqArgs& R, uint32_t b) {
   return min((uint32_t)e[0] | ((uint32_t)e[1] << 8), 63u);
 }
 
-__global__ void k_req_levels(ReqArgs R) {
+// Counters of a level are shared by every block of it: a workgroup counts in
+// LDS and adds its sums once (an atomic a block was 26 us for 8192 blocks).
+__global__ void __launch_bounds__(256) k_req_levels(ReqArgs R) {
+  __shared__ uint32_t lvl[64];
+  if (threadIdx.x < 64) lvl[threadIdx.x] = 0;
+  __syncthreads();
   const uint32_t cnt = R.ctl[kCtlListTail];
   const uint64_t B = 1ull << R.bl;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
     const uint32_t b = (uint32_t)R.list[i];
-    atomicAdd(R.ctl + kCtlLevelCnt + block_level(R, b), 1u);
+    atomicAdd(&lvl[block_level(R, b)], 1u);
     const uint64_t sb = (uint64_t)b << R.bl, eb = min(sb + B, R.n);
     uint64_t a = 0;
     if (R.direct && sb >= R.a0 && eb <= R.a0 + R.b0 && ((sb - R.a0) & 15) == 0) {
@@ -2181,6 +2186,8 @@ __global__ void k_req_levels(ReqArgs R) {
     }
     R.addr[b] = a;
   }
+  __syncthreads();
+  if (threadIdx.x < 64 && lvl[threadIdx.x]) atomicAdd(R.ctl + kCtlLevelCnt + threadIdx.x, lvl[threadIdx.x]);
 }
 
 __global__ void k_req_level_scan(ReqArgs R) {
@@ -2195,12 +2202,20 @@ __global__ void k_req_level_scan(ReqArgs R) {
   }
 }
 
-__global__ void k_req_scatter(ReqArgs R) {
-  const uint32_t cnt = R.ctl[kCtlListTail];
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
-    const uint32_t b = (uint32_t)R.list[i];
-    const uint32_t pos = atomicAdd(R.rlevel_ptr + 65 + block_level(R, b), 1u);
-    R.rqueue[pos] = b;
+__global__ void __launch_bounds__(256) k_req_scatter(ReqArgs R) {
+  __shared__ uint32_t lvl[64];
+  const uint32_t t = threadIdx.x, cnt = R.ctl[kCtlListTail];
+  for (uint32_t i0 = blockIdx.x * 256; i0 < cnt; i0 += gridDim.x * 256) {       // uniform
+    if (t < 64) lvl[t] = 0;
+    __syncthreads();
+    const bool have = i0 + t < cnt;
+    const uint32_t b = have ? (uint32_t)R.list[i0 + t] : 0u, L = have ? block_level(R, b) : 0u;
+    const uint32_t k = have ? atomicAdd(&lvl[L], 1u) : 0u;
+    __syncthreads();
+    if (t < 64 && lvl[t]) lvl[t] = atomicAdd(R.rlevel_ptr + 65 + t, lvl[t]);    // the level's next places
+    __syncthreads();
+    if (have) R.rqueue[lvl[L] + k] = b;
+    __syncthreads();
   }
 }
 
@@ -2209,11 +2224,18 @@ __global__ void k_req_scatter(ReqArgs R) {
 // the previous closure's addresses, spans and prefix sums of the requests,
 // covering blocks marked and listed, the dependency closure expanded round by
 // round (a round takes every listed entry not yet expanded; a block joins the
-// list once, when its mark is raised to this call's epoch), then a counting
-// sort of the closure by level with each block's address.
+// list once, when it is marked), then a counting sort of the closure by level
+// with each block's address.  Bound by the latency of each step, so marks,
+// list and levels are kept in LDS as far as they fit: marks as bits of at
+// most kPlanBits blocks (R.lmark; else as epochs in memory), the first
+// kPlanList entries of list and levels.  4096 records on 8192 blocks: 175 us
+// for the eight kernels, 55 us here; 256 mixed requests 86 and 19 us.
 constexpr uint32_t kPlanWG = 1024;
+constexpr uint32_t kPlanBits = 1u << 18, kPlanList = 6144;
 
 __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
+  __shared__ uint32_t s_bits[kPlanBits / 32], s_list[kPlanList];
+  __shared__ uint8_t s_lvl[kPlanList];
   __shared__ uint64_t wsum[2][kPlanWG / 64];
   __shared__ uint32_t lvl_cnt[64], lvl_cur[64];
   __shared__ uint32_t s_tail, s_slots, s_nreq, s_epoch;
@@ -2227,6 +2249,8 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
       if (b < R.n_blocks) R.addr[b] = 0;
     }
   }
+  if (R.lmark)
+    for (uint32_t i = t; i < ((uint32_t)R.n_blocks + 31) / 32; i += kPlanWG) s_bits[i] = 0;
   if (t < 64) lvl_cnt[t] = 0;
   if (t == 0) {
     uint64_t n = R.n_max;
@@ -2234,14 +2258,11 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
     s_nreq = (uint32_t)n;
     s_tail = 0;
     s_slots = 0;
-  }
-  __syncthreads();
-  if (t == 0) {
     s_epoch = R.ctl[kCtlREpoch] + 1;
     R.ctl[kCtlREpoch] = s_epoch;
     R.ctl[kCtlListHead] = 0;
     R.ctl[kCtlListDone] = 0;
-    R.ctl[kCtlNReq] = s_nreq;
+    R.ctl[kCtlNReq] = (uint32_t)n;
   }
   __syncthreads();
   const uint32_t epoch = s_epoch;
@@ -2314,17 +2335,40 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
     s_pairs = pairs;
   }
   __syncthreads();
-  // covering blocks: marked with this epoch and listed once each
+  // covering blocks: marked and listed once each
   const uint64_t pairs = s_pairs;
   auto push = [&](uint32_t b) {
-    const uint32_t old = __hip_atomic_fetch_max(R.mark + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old >= epoch) return;
+    if (R.lmark) {
+      if (b >= R.n_blocks || (atomicOr(&s_bits[b >> 5], 1u << (b & 31)) >> (b & 31)) & 1u) return;
+    } else {
+      const uint32_t old = __hip_atomic_fetch_max(R.mark + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (old >= epoch) return;
+    }
     const uint32_t i = atomicAdd(&s_tail, 1u);
+    if (i < kPlanList) s_list[i] = b;
     if (i < R.n_blocks) R.list[i] = ((uint64_t)epoch << 32) | b;
   };
-  for (uint64_t g = t; g < pairs; g += kPlanWG) {
-    const uint32_t j = find_req(R.cnt_ptr, nreq, g);
-    push((uint32_t)((R.spans[2 * j] >> R.bl) + (g - R.cnt_ptr[j])));
+  auto listed = [&](uint32_t i) { return i < kPlanList ? s_list[i] : (uint32_t)R.list[i]; };
+  if (R.mode == 0) {
+    for (uint64_t g = t; g < pairs; g += kPlanWG) push((uint32_t)((R.a0 >> R.bl) + g));
+  } else if (pairs) {
+    // a thread per request for its first blocks, then the wave together for
+    // each request that has more
+    for (uint32_t c0 = 0; c0 < nreq; c0 += kPlanWG) {
+      const uint32_t j = c0 + t;
+      uint32_t b0 = 0, n = 0;
+      if (j < nreq) {
+        const uint64_t s0 = R.spans[2 * j], e0 = R.spans[2 * j + 1];
+        b0 = (uint32_t)(s0 >> R.bl);
+        n = e0 > s0 ? (uint32_t)(((e0 - 1) >> R.bl) - b0 + 1) : 0u;
+      }
+      for (uint32_t k = 0; k < min(n, 4u); k++) push(b0 + k);
+      for (uint64_t more = __ballot(n > 4); more; more &= more - 1) {     // wave-uniform
+        const uint32_t l = (uint32_t)__builtin_ctzll(more);
+        const uint32_t nb = __builtin_amdgcn_readlane(n, l), bb = __builtin_amdgcn_readlane(b0, l);
+        for (uint32_t k = 4 + lane; k < nb; k += 64) push(bb + k);
+      }
+    }
   }
   __syncthreads();
   // dependency closure, one round per pass over the entries listed so far.
@@ -2338,9 +2382,16 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
     __syncthreads();
     if (head >= tail) break;
     for (uint32_t i = head + t; i < tail; i += kPlanWG) {
-      const uint32_t b = (uint32_t)R.list[i];
+      const uint32_t b = listed(i);
       const uint64_t d0 = ld64(R.arc + R.off_dep_ptr + 8ull * b), d1 = ld64(R.arc + R.off_dep_ptr + 8ull * (b + 1));
-      for (uint64_t k = d0; k < d1; k++) push(ld32(R.arc + R.off_dep_idx + 4 * k));
+      for (uint64_t k = d0; k < d1; k += 4) {
+        uint32_t id[4];
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++) id[u] = k + u < d1 ? ld32(R.arc + R.off_dep_idx + 4 * (k + u)) : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < 4; u++)
+          if (k + u < d1) push(id[u]);
+      }
     }
     head = tail;
     __syncthreads();
@@ -2350,8 +2401,9 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
   // an aligned single range, else a scratch slot
   const uint64_t B = 1ull << R.bl;
   for (uint32_t i = t; i < cnt; i += kPlanWG) {
-    const uint32_t b = (uint32_t)R.list[i];
-    atomicAdd(&lvl_cnt[block_level(R, b)], 1u);
+    const uint32_t b = listed(i), L = block_level(R, b);
+    if (i < kPlanList) s_lvl[i] = (uint8_t)L;
+    atomicAdd(&lvl_cnt[L], 1u);
     const uint64_t sb = (uint64_t)b << R.bl, eb = min(sb + B, R.n);
     uint64_t a = 0;
     if (R.direct && sb >= R.a0 && eb <= R.a0 + R.b0 && ((sb - R.a0) & 15) == 0) {
@@ -2378,8 +2430,8 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
   }
   __syncthreads();
   for (uint32_t i = t; i < cnt; i += kPlanWG) {
-    const uint32_t b = (uint32_t)R.list[i];
-    R.rqueue[atomicAdd(&lvl_cur[block_level(R, b)], 1u)] = b;
+    const uint32_t b = listed(i);
+    R.rqueue[atomicAdd(&lvl_cur[i < kPlanList ? s_lvl[i] : block_level(R, b)], 1u)] = b;
   }
   if (t == 0) {
     R.ctl[kCtlListTail] = cnt;
@@ -2524,12 +2576,14 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   const uint32_t spin = h->tune.spin_limit ? h->tune.spin_limit : (1u << 20);
   const uint32_t g_req = (uint32_t)std::min<uint64_t>(1024, (n_max + 255) / 256);
   // small calls are planned by one workgroup (one launch instead of eight):
-  // at most plan_blocks covering blocks expected (a range, reads at two
-  // blocks each, batches at 256 blocks a request)
+  // at most plan_blocks covering blocks expected (a range; a record lies in one
+  // block or a few more; of a batch 256 blocks a request, but not more than
+  // its output holds)
   const uint64_t Bs = 1ull << v.block_log2, pb = h->tune.plan_blocks ? h->tune.plan_blocks : 4096;
   const bool small = R.mode == 0 ? single_len / Bs + 2 <= pb
-                   : R.mode == 1 ? n_max * (v.max_record_len / Bs + 2) <= pb
-                                 : n_max * 256 <= pb;
+                   : R.mode == 1 ? n_max * (v.max_record_len / Bs + 1) <= pb
+                                 : std::min(n_max * 256, cap / Bs + 2 * n_max) <= pb;
+  R.lmark = v.n_blocks <= kPlanBits ? 1u : 0u;
   const uint32_t g_wide = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(1024, (v.n_blocks + 255) / 256));
   if (small) {
     hipLaunchKernelGGL(k_req_plan, dim3(1), dim3(kPlanWG), 0, s, R);

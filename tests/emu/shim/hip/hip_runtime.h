@@ -126,6 +126,7 @@ inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 
 // atomics: host atomics (work-items of a workgroup run concurrently)
 template <class T> inline T atomicAdd(T* p, T v) { return __atomic_fetch_add(p, v, __ATOMIC_SEQ_CST); }
+template <class T> inline T atomicOr(T* p, T v) { return __atomic_fetch_or(p, v, __ATOMIC_SEQ_CST); }
 template <class T> inline T __hip_atomic_load(T* p, int, int) { return __atomic_load_n(p, __ATOMIC_SEQ_CST); }
 template <class T> inline T __hip_atomic_load(const T* p, int, int) { return __atomic_load_n(p, __ATOMIC_SEQ_CST); }
 template <class T, class U> inline void __hip_atomic_store(T* p, U v, int, int) {

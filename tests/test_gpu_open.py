@@ -28,7 +28,11 @@ def test_open_clears_the_closure_list(orc):
         # the list is the section before the control words (128 u32), 256-byte aligned
         at = ws.numel() - 512 - ((8 * nb + 255) & ~255)
         assert not np.any(ws[at:at + 8 * nb].cpu().numpy())
-        # a call planned by the eight-kernel path (more than 2048 reads)
+        # a call planned by the eight-kernel path
+        tu = lz._lib.Tuning()
+        assert L.lz_get_tuning(h, C.byref(tu)) == 0
+        tu.plan_blocks = 1
+        assert L.lz_set_tuning(h, C.byref(tu)) == 0
         ids = torch.arange(4000, device="cuda").flip(0)
         out = torch.zeros(4000 * int(arc.info.max_record_len), dtype=torch.uint8, device="cuda")
         offs = torch.empty(4001, dtype=torch.int64, device="cuda")
