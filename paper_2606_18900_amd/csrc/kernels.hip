@@ -30,6 +30,7 @@
 
 #include <cstdint>
 
+#include "lz_device.h"
 #include "lz_internal.h"
 
 namespace {
@@ -139,46 +140,11 @@ struct DevArgs {
   const uint64_t* addr;     // request mode: per-block device address, or null
   uint32_t* flags;          // per block: the epoch it was last decoded in
   uint32_t* ctl;
+  uint32_t wg0, nwg;        // the launch's workgroups wg0 .. wg0 + nwg - 1 decode this archive
   uint32_t flow;            // 1, 2: blocks by ticket, ordered by completion flags (2: blocks
                             // share cache lines of the output)
   uint32_t spin_limit;
 };
-
-// Loads and stores at any address, in global memory and in LDS (one access
-// each: the device takes unaligned ones)
-typedef uint32_t u32x4 __attribute__((vector_size(16)));
-typedef uint32_t u32x2 __attribute__((vector_size(8)));
-template <class T> struct __attribute__((packed)) Any { T v; };
-template <class T> __device__ __forceinline__ T ld_any(const uint8_t* p) { return reinterpret_cast<const Any<T>*>(p)->v; }
-template <class T> __device__ __forceinline__ void st_any(uint8_t* p, T v) { reinterpret_cast<Any<T>*>(p)->v = v; }
-__device__ __forceinline__ uint32_t ld32(const uint8_t* p) { return ld_any<uint32_t>(p); }
-__device__ __forceinline__ uint64_t ld64(const uint8_t* p) { return ld_any<uint64_t>(p); }
-__device__ __forceinline__ u32x4 ld128(const uint8_t* p) { return ld_any<u32x4>(p); }
-// the first n <= 16 bytes of v to p
-__device__ __forceinline__ void st_upto16(uint8_t* p, u32x4 v, uint32_t n) {
-  if (n == 16) {
-    st_any<u32x4>(p, v);
-    return;
-  }
-  uint32_t a = v[0], b = v[1];
-  if (n & 8) {
-    st_any<u32x2>(p, (u32x2){a, b});
-    p += 8;
-    a = v[2];
-    b = v[3];
-  }
-  if (n & 4) {
-    st_any<uint32_t>(p, a);
-    p += 4;
-    a = b;
-  }
-  if (n & 2) {
-    st_any<uint16_t>(p, (uint16_t)a);
-    p += 2;
-    a >>= 16;
-  }
-  if (n & 1) *p = (uint8_t)a;
-}
 
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63; }
 // 16 bytes per lane straight from global memory into LDS, without registers
@@ -1067,7 +1033,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     // the workgroup's next place; the literal decode hides the ticket's round
     // trip (several microseconds while every workgroup takes them; taken
     // during the preparation, one block further ahead, it held that up)
-    uint32_t nit = it + gridDim.x, nbq = ~0u;
+    uint32_t nit = it + A.nwg, nbq = ~0u;
     if (A.flow && t == 64) nit = take_ticket(A);
     if (wv < Glit) {
       const uint32_t g = wv;
@@ -1511,8 +1477,20 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
 // 432 and 306, 64 MiB FASTQ of 64 levels 1763 and 595, one record 135 and 64.
 // Otherwise a grid-stride slice of the queue's blocks q_begin .. q_end (one
 // level).
-__global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per SIMD: at most 168 VGPRs
+// Jobs: up to four archives in one launch (the streams of a split container).
+template <uint32_t N>
+struct Jobs {
+  DevArgs a[N];
+};
+
+template <uint32_t N>
+__global__ void __launch_bounds__(kWG, 3) k_decode(Jobs<N> J) {   // 3 waves per SIMD: at most 168 VGPRs
   __shared__ Smem S;
+  uint32_t job = 0;
+  if (N > 1)
+    while (job + 1 < N && blockIdx.x >= J.a[job].wg0 + J.a[job].nwg) job++;
+  const DevArgs& A = J.a[N > 1 ? job : 0];
+  const uint32_t wg = blockIdx.x - A.wg0;
   // issue priority: 1 by default, 2 for wave 0's in-block passes, 0 for the
   // next block's preparation by waves 1..3 (the one stage with slack)
   __builtin_amdgcn_s_setprio(1);
@@ -1523,7 +1501,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
     qe = A.qptr[A.q_end];
   }
   const uint32_t total = qe - qb;
-  if (blockIdx.x >= total) return;         // more workgroups than blocks
+  if (wg >= total) return;                 // more workgroups than blocks
   if (A.flow && t == 0) S.nit = take_ticket(A);
 #ifdef LZ_STAGE_CLOCKS
   if (t < kClkSlots) S.clk[t] = 0;
@@ -1531,7 +1509,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
   const uint32_t epoch = A.flow ? A.ctl[kCtlEpoch] + 1 : 0u;
   load_tables(S, A);
   __syncthreads();
-  uint32_t it = A.flow ? uni(S.nit) : blockIdx.x;
+  uint32_t it = A.flow ? uni(S.nit) : wg;
   uint32_t b = it < total ? A.queue[qb + it] : 0u;
   bool prepared = false;      // the block's stages 0 and 1 are done
   while (it < total) {
@@ -1548,7 +1526,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
       it = uni(S.nit);
       b = uni(S.nb);
     } else {                               // corrupt block: no ticket was taken
-      if (t == 0) S.nit = A.flow ? take_ticket(A) : it + gridDim.x;
+      if (t == 0) S.nit = A.flow ? take_ticket(A) : it + A.nwg;
       __syncthreads();
       it = uni(S.nit);
       b = it < total ? A.queue[qb + it] : 0u;
@@ -1557,7 +1535,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(DevArgs A) {   // 3 waves per
   }
   if (A.flow && t == 0) {
     const uint32_t left = __hip_atomic_fetch_add(A.ctl + kCtlLeft, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (left + 1 == min(gridDim.x, total)) {
+    if (left + 1 == min(A.nwg, total)) {
       A.ctl[kCtlTicket] = 0;
       A.ctl[kCtlLeft] = 0;
       A.ctl[kCtlEpoch] = epoch;
@@ -1658,30 +1636,75 @@ static uint32_t flow_mode(const DevArgs& A, uint64_t at) {
   return A.bl >= 7 && (at & 127) == 0 ? 1u : 2u;
 }
 
-int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
+// One archive on the first nwg workgroups.
+static void launch_decode(DevArgs A, uint32_t nwg, hipStream_t s) {
+  A.wg0 = 0;
+  A.nwg = nwg;
+  hipLaunchKernelGGL(k_decode<1>, dim3(nwg), dim3(kWG), 0, s, Jobs<1>{{A}});
+}
+
+static uint32_t decode_slots(const lz_handle* h) { return (uint32_t)(h->n_cu * std::max(1u, h->tune.wg_per_cu)); }
+
+// The whole file in one launch: by ticket, or, of one level, where nothing
+// waits and tickets are all overhead, in static slices (32 MiB of noise,
+// stored blocks: 112 us by ticket, 68 us in slices).
+static DevArgs whole_file(const lz_handle* h, uint8_t* out) {
   DevArgs A = make_args(h);
   A.queue = h->ws.queue;
   A.out = out;
-  const uint32_t slots = (uint32_t)(h->n_cu * std::max(1u, h->tune.wg_per_cu));
-  // one level: nothing to wait for, and tickets are all overhead (32 MiB of
-  // noise, stored blocks: 112 us by ticket, 68 us in static slices)
-  if (h->tune.sync_mode == 0 && h->av.n_levels > 1) {
-    A.flow = flow_mode(A, reinterpret_cast<uintptr_t>(out));
-    A.q_end = (uint32_t)h->av.n_blocks;
-    hipLaunchKernelGGL(k_decode, dim3(std::min(A.q_end, slots)), dim3(kWG), 0, s, A);
+  A.flow = h->av.n_levels > 1 ? flow_mode(A, reinterpret_cast<uintptr_t>(out)) : 0u;
+  A.q_end = (uint32_t)h->av.n_blocks;
+  return A;
+}
+
+int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
+  DevArgs A = whole_file(h, out);
+  const uint32_t slots = decode_slots(h);
+  if (h->tune.sync_mode == 0) {
+    launch_decode(A, std::min(A.q_end, slots), s);
     return launch_ok("lz_decode_all");
   }
+  A.flow = 0;
   uint32_t base = 0;
   for (uint32_t L = 0; L < h->av.n_levels; L++) {
     const uint32_t c = h->level_count[L];
     if (c) {
       A.q_begin = base;
       A.q_end = base + c;
-      hipLaunchKernelGGL(k_decode, dim3(std::min(c, slots)), dim3(kWG), 0, s, A);
+      launch_decode(A, std::min(c, slots), s);
     }
     base += c;
   }
   return launch_ok("lz_decode_all");
+}
+
+// Whole-file decodes of n <= 4 non-empty archives at once, out[k] the output
+// of h[k].  Workgroups are shared out by blocks, at least sixteen an archive
+// (a short one with many levels is a chain that two or three can follow), the
+// deepest archive first: one after the other, the streams of a 64 MiB FASTQ
+// took 51 + 96 + 181 + 104 us, the 181 for 25 blocks in 34 levels.
+int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, hipStream_t s) {
+  Jobs<4> J{};
+  uint32_t at[4], m = 0;
+  uint64_t blocks = 0;
+  for (uint32_t k = 0; k < n; k++) {
+    uint32_t i = m++;
+    for (; i && h[at[i - 1]]->av.n_levels < h[k]->av.n_levels; i--) at[i] = at[i - 1];
+    at[i] = k;
+    blocks += h[k]->av.n_blocks;
+  }
+  uint32_t wg = 0;
+  for (uint32_t k = 0; k < m; k++) {
+    const lz_handle* a = h[at[k]];
+    const uint64_t share = decode_slots(a) * a->av.n_blocks / blocks;
+    J.a[k] = whole_file(a, out[at[k]]);
+    J.a[k].wg0 = wg;
+    J.a[k].nwg = (uint32_t)std::min<uint64_t>(a->av.n_blocks, std::max<uint64_t>(share, 16));
+    wg += J.a[k].nwg;
+  }
+  for (uint32_t k = m; k < 4; k++) J.a[k].wg0 = wg;      // no workgroups
+  if (wg) hipLaunchKernelGGL(k_decode<4>, dim3(wg), dim3(kWG), 0, s, J);
+  return launch_ok("lz_split_decode_all");
 }
 
 // ---- verification: per-block FNV-1a-64 against the directory -----------------
@@ -2603,20 +2626,19 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   A.qptr = h->ws.rlevel_ptr;
   A.addr = h->ws.addr;
   A.out = d_out;
-  const uint32_t slots = (uint32_t)(h->n_cu * std::max(1u, h->tune.wg_per_cu));
-  const uint32_t grid = (uint32_t)std::min<uint64_t>(slots, std::max<uint64_t>(1, v.n_blocks));
+  const uint32_t grid = (uint32_t)std::min<uint64_t>(decode_slots(h), std::max<uint64_t>(1, v.n_blocks));
   if (h->tune.req_sync_mode == 0 && v.n_levels > 1) {
     // scratch slots are whole lines; blocks decoded straight into the output lie
     // at d_out - single_off plus a multiple of the block size
     const uint64_t at = reinterpret_cast<uintptr_t>(d_out) - single_off;
     A.flow = flow_mode(A, R.direct && (at & 15) == 0 ? at : 0);
     A.q_end = kMaxLevels;                  // rlevel_ptr[0] .. rlevel_ptr[64]: the whole closure
-    hipLaunchKernelGGL(k_decode, dim3(grid), dim3(kWG), 0, s, A);
+    launch_decode(A, grid, s);
   } else {
     for (uint32_t L = 0; L < v.n_levels; L++) {
       A.q_begin = L;
       A.q_end = L + 1;
-      hipLaunchKernelGGL(k_decode, dim3(grid), dim3(kWG), 0, s, A);
+      launch_decode(A, grid, s);
     }
   }
   // gather: a wave copies up to a quarter of a block (4 KiB in flight); records

@@ -30,13 +30,17 @@
 #include <vector>
 
 #include "lz.h"
+#include "lz_device.h"
 #include "lz_internal.h"
+
+int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, hipStream_t s);   // kernels.hip
 
 namespace {
 
 constexpr uint64_t kSplitHeader = 128;
 constexpr uint32_t kSplitVersion = 2, kSplitFlags = 3;
-constexpr uint32_t kJoinWG = 256;               // one wave per record
+constexpr uint32_t kJoinWG = 256;               // half a wave per record
+constexpr uint32_t kJoinLanes = 32;
 
 uint64_t rd64(const uint8_t* p) { uint64_t v; std::memcpy(&v, p, 8); return v; }
 uint32_t rd32(const uint8_t* p) { uint32_t v; std::memcpy(&v, p, 4); return v; }
@@ -98,22 +102,51 @@ struct JoinArgs {
   uint8_t* out;
 };
 
-// Records [r0, r1) back in file order, clipped to [lo, hi): one wave per
-// record (grid-stride), each line copied byte by byte with consecutive lanes
-// on consecutive bytes.
+// A record's four lines, one after the other to dst, by the kJoinLanes lanes
+// that call it with l = 0, 1, ...: 16 bytes a lane at any alignment, the last
+// piece of a line of 16 bytes or more moved back to end with it (its overlap
+// written twice with the same bytes).  A line of less is loaded as 16 bytes
+// all the same: 15 bytes past it lie in the caller's buffer too.  A 150 bp
+// record is 23 pieces, so every lane has one load and one store: bound by
+// memory, where byte copies (82 us for 64 MiB) were bound by instructions.
+struct Line {
+  const uint8_t* p;
+  uint64_t n;
+};
+__device__ __forceinline__ void put_lines(uint8_t* dst, Line h, Line s, Line p, Line q, uint32_t l) {
+  const uint64_t f1 = (h.n + 15) >> 4, f2 = f1 + ((s.n + 15) >> 4), f3 = f2 + ((p.n + 15) >> 4),
+                 all = f3 + ((q.n + 15) >> 4);                     // pieces before each line
+  for (uint64_t i = l; i < all; i += kJoinLanes) {
+    Line x = h;
+    uint64_t at = 0, k = i;
+    if (i >= f1) { x = s; at = h.n; k = i - f1; }
+    if (i >= f2) { x = p; at = h.n + s.n; k = i - f2; }
+    if (i >= f3) { x = q; at = h.n + s.n + p.n; k = i - f3; }
+    const uint64_t o = x.n >= 16 ? min(16 * k, x.n - 16) : 0;
+    st_upto16(dst + at + o, ld128(x.p + o), (uint32_t)min(x.n, (uint64_t)16));
+  }
+}
+
+// Records [r0, r1) back in file order, clipped to [lo, hi): half a wave per
+// record (grid-stride); records cut by the clip, at most two, byte by byte.
 __global__ void __launch_bounds__(kJoinWG) k_split_join(JoinArgs J) {
-  const uint32_t lane = threadIdx.x & 63;
-  const uint64_t waves = (uint64_t)gridDim.x * (kJoinWG / 64);
-  for (uint64_t i = J.r0 + (uint64_t)blockIdx.x * (kJoinWG / 64) + (threadIdx.x >> 6); i < J.r1; i += waves) {
+  const uint32_t l = threadIdx.x % kJoinLanes;
+  const uint64_t step = (uint64_t)gridDim.x * (kJoinWG / kJoinLanes);
+  for (uint64_t i = J.r0 + (uint64_t)blockIdx.x * (kJoinWG / kJoinLanes) + threadIdx.x / kJoinLanes; i < J.r1; i += step) {
     const uint64_t h0 = J.hs[i], h1 = J.hs[i + 1], s0 = J.ss[i], s1 = J.ss[i + 1];
     uint64_t pos = h0 + 2 * s0 + 2 * i;                 // the record's first byte in the file
     const uint64_t beg[4] = {h0, s0, 2 * i, s0};
     const uint64_t len[4] = {h1 - h0, s1 - s0, 2, s1 - s0};
+    auto line = [&](int k) { return Line{J.src[k] + (beg[k] - J.base[k]), len[k]}; };
+    if (pos >= J.lo && pos + len[0] + 2 * len[1] + 2 <= J.hi) {
+      put_lines(J.out + (pos - J.lo), line(0), line(1), line(2), line(3), l);
+      continue;
+    }
 #pragma unroll
     for (int k = 0; k < 4; k++) {
-      const uint8_t* src = J.src[k] + (beg[k] - J.base[k]);
       const uint64_t a = max(pos, J.lo), b = min(pos + len[k], J.hi);
-      for (uint64_t p = a + lane; p < b; p += 64) J.out[p - J.lo] = src[p - pos];
+      const uint8_t* src = J.src[k] + (beg[k] - J.base[k]);
+      for (uint64_t p = a + l; p < b; p += kJoinLanes) J.out[p - J.lo] = src[p - pos];
       pos += len[k];
     }
   }
@@ -156,21 +189,17 @@ struct GatherArgs {
   uint64_t* offsets;            // n + 1: record k at out[offsets[k] .. offsets[k+1])
 };
 
-// Record k = its four lines from the streams' batch outputs; one wave per
+// Record k = its four lines from the streams' batch outputs; half a wave per
 // record (grid-stride).
 __global__ void __launch_bounds__(kJoinWG) k_split_gather(GatherArgs G) {
-  const uint32_t lane = threadIdx.x & 63;
-  const uint64_t waves = (uint64_t)gridDim.x * (kJoinWG / 64);
-  for (uint64_t k = (uint64_t)blockIdx.x * (kJoinWG / 64) + (threadIdx.x >> 6); k <= G.n; k += waves) {
-    uint64_t o = G.poff[0][k] + G.poff[1][k] + G.poff[2][k] + G.poff[3][k];
-    if (lane == 0) G.offsets[k] = o;
+  const uint32_t l = threadIdx.x % kJoinLanes;
+  const uint64_t step = (uint64_t)gridDim.x * (kJoinWG / kJoinLanes);
+  for (uint64_t k = (uint64_t)blockIdx.x * (kJoinWG / kJoinLanes) + threadIdx.x / kJoinLanes; k <= G.n; k += step) {
+    const uint64_t o = G.poff[0][k] + G.poff[1][k] + G.poff[2][k] + G.poff[3][k];
+    if (l == 0) G.offsets[k] = o;
     if (k == G.n) continue;
-#pragma unroll
-    for (int j = 0; j < 4; j++) {
-      const uint64_t a = G.poff[j][k], len = G.poff[j][k + 1] - a;
-      for (uint64_t p = lane; p < len; p += 64) G.out[o + p] = G.piece[j][a + p];
-      o += len;
-    }
+    auto line = [&](int j) { return Line{G.piece[j] + G.poff[j][k], G.poff[j][k + 1] - G.poff[j][k]}; };
+    put_lines(G.out + o, line(0), line(1), line(2), line(3), l);
   }
 }
 
@@ -420,7 +449,7 @@ int launch_join(lz_split* sp, uint64_t r0, uint64_t r1, const uint64_t beg[4], u
   J.lo = lo;
   J.hi = hi;
   J.out = out;
-  const uint64_t need = (r1 - r0 + kJoinWG / 64 - 1) / (kJoinWG / 64);
+  const uint64_t need = (r1 - r0 + kJoinWG / kJoinLanes - 1) / (kJoinWG / kJoinLanes);
   const uint32_t grid = (uint32_t)std::min<uint64_t>(need, sp->grid);
   hipLaunchKernelGGL(k_split_join, dim3(grid), dim3(kJoinWG), 0, s, J);
   return hip_ok(hipGetLastError(), "k_split_join");
@@ -431,11 +460,19 @@ int launch_join(lz_split* sp, uint64_t r0, uint64_t r1, const uint64_t beg[4], u
 extern "C" int lz_split_decode_all(lz_split* sp, uint8_t* d_out, uint64_t cap, hipStream_t s) {
   if (!sp || (!d_out && sp->hd.n)) return lz_fail(LZ_EINVAL, "lz_split_decode_all: null argument");
   if (cap < sp->hd.n) return lz_fail(LZ_ECAPACITY, "lz_split_decode_all: output needs %llu bytes", (unsigned long long)sp->hd.n);
+  lz_handle* h[4];
+  uint8_t* out[4];
+  uint32_t n = 0;
+  bool together = true;                     // every stream in its default launch mode
   for (int k = 0; k < 4; k++) {
     if (!sp->slen[k]) continue;
-    const int rc = lz_decode_all(sp->sub[k], sp->buf + sp->base[k], sp->slen[k], s);
-    if (rc) return rc;
+    h[n] = sp->sub[k];
+    out[n++] = sp->buf + sp->base[k];
+    together &= sp->sub[k]->tune.sync_mode == 0;
   }
+  int rc = together && n ? lz_launch_decode_many(h, out, n, s) : LZ_OK;
+  for (uint32_t k = 0; k < n && !together && !rc; k++) rc = lz_decode_all(h[k], out[k], h[k]->av.n, s);
+  if (rc) return rc;
   const uint64_t beg[4] = {0, 0, 0, 0};
   return launch_join(sp, 0, sp->hd.n_reads, beg, 0, sp->hd.n, d_out, s);
 }
@@ -516,7 +553,7 @@ extern "C" int lz_split_read_lookup(lz_split* sp, const int64_t* d_ids, uint64_t
   G.n = n;
   G.out = d_out;
   G.offsets = d_offsets;
-  const uint32_t grid = (uint32_t)std::min<uint64_t>((n + 1 + 3) / 4, sp->grid);
+  const uint32_t grid = (uint32_t)std::min<uint64_t>((n + 1 + kJoinWG / kJoinLanes - 1) / (kJoinWG / kJoinLanes), sp->grid);
   hipLaunchKernelGGL(k_split_gather, dim3(grid), dim3(kJoinWG), 0, s, G);
   return hip_ok(hipGetLastError(), "k_split_gather");
 }
