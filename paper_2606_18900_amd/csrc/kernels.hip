@@ -621,21 +621,28 @@ __device__ __forceinline__ BlockDir block_dir(const DevArgs& A, uint32_t b) {
   return d;
 }
 
-// The four stream records (CMD, MLEN, OFF, LIT) parsed and checked from the
-// LDS copy hp of the block's first hlen payload bytes (every thread parses
-// the same bytes, so the result is wave-uniform).
+// The first n of the four stream records (CMD, MLEN, OFF, LIT) parsed and
+// checked from the LDS copy hp of the block's first hlen payload bytes (every
+// thread parses the same bytes, so the result is wave-uniform).
 __device__ __forceinline__ bool parse_records(const DevArgs& A, const BlockDir& d, const uint8_t* hp,
-                                              uint32_t hlen, Stream& sc, Stream& sm, Stream& so,
-                                              Stream& sl) {
+                                              uint32_t hlen, uint32_t n, Stream& sc, Stream& sm,
+                                              Stream& so, Stream& sl) {
   uint32_t off = 0;
   bool ok = d.ns >= 1 && d.ns <= kMaxSeq && d.nlit <= d.blen && (d.poff & 15) == 0;
   ok &= parse_stream(hp, hlen, d.plen, &off, 2 * d.ns, A.seq_lanes, true, sc);
-  ok &= parse_stream(hp, hlen, d.plen, &off, 2 * d.ns, A.seq_lanes, true, sm);
-  ok &= parse_stream(hp, hlen, d.plen, &off, A.w * d.ns, A.seq_lanes, true, so);
-  ok &= parse_stream(hp, hlen, d.plen, &off, d.nlit, A.lit_lanes, false, sl);
+  if (n > 1) ok &= parse_stream(hp, hlen, d.plen, &off, 2 * d.ns, A.seq_lanes, true, sm);
+  if (n > 2) {
+    ok &= parse_stream(hp, hlen, d.plen, &off, A.w * d.ns, A.seq_lanes, true, so);
+    ok &= parse_stream(hp, hlen, d.plen, &off, d.nlit, A.lit_lanes, false, sl);
+  }
   if (!ok) return false;
-  const bool c0 = counts_ok(hp, sc), c1 = counts_ok(hp, sm), c2 = counts_ok(hp, so), c3 = counts_ok(hp, sl);
-  return c0 & c1 & c2 & c3;
+  ok = counts_ok(hp, sc);
+  if (n > 1) ok &= counts_ok(hp, sm);
+  if (n > 2) {
+    const bool a = counts_ok(hp, so), b = counts_ok(hp, sl);
+    ok &= a & b;
+  }
+  return ok;
 }
 
 // Short stream `role` of a block with ns sequences, by one wave: 0 CMD ->
@@ -762,7 +769,7 @@ __device__ __forceinline__ void prep_tile(Smem& S, const DevArgs& A, uint32_t b)
   __syncthreads();
   CLK_MARK(S, 0);
   Stream sc, sm, so, sl;
-  const bool ok = parse_records(A, d, S.tile, hlen, sc, sm, so, sl);
+  const bool ok = parse_records(A, d, S.tile, hlen, 4, sc, sm, so, sl);
   if (t == 0) {
     S.pok = ok ? 1u : 0u;
     put_prep(S, d, sl, S.tile, ok);
@@ -809,21 +816,23 @@ __device__ __forceinline__ void prep_ring(Smem& S, const DevArgs& A, uint32_t b)
       uint4* dst4 = reinterpret_cast<uint4*>(S.prep);
       for (uint32_t c = lane; c < n16; c += 64) dst4[c] = src4[c];
     }
-    if (wv == 1) put_deps(S, A, dp);
+    if (wv == 3) put_deps(S, A, dp);
     vm_wait();
     if (tail) S.prep[(hlen & ~15u) + lane] = (uint8_t)tb;
   }
   __builtin_amdgcn_wave_barrier();
   Stream sc, sm, so, sl;
-  const bool ok = parse_records(A, d, S.prep, hlen, sc, sm, so, sl);
+  // each wave as many records as it needs; wave 3, whose OFF stream is mostly
+  // stored and soon done, all four and the bookkeeping
+  const uint32_t role = wv - 1;
+  const bool ok = parse_records(A, d, S.prep, hlen, role < 2 ? role + 1 : 4u, sc, sm, so, sl);
   bool okw = true;
   if (ok) {
-    const uint32_t role = wv - 1;
     const Stream& s = role == 0 ? sc : (role == 1 ? sm : so);
     okw = short_stream(S, A, role, s, S.prep, d.ns);
   }
-  if (ok && lane == 0) S.perr[wv - 1] = okw ? 0u : 1u;
-  if (wv == 1 && lane == 0) {
+  if (ok && lane == 0) S.perr[role] = okw ? 0u : 1u;
+  if (wv == 3 && lane == 0) {
     S.pok = ok ? 1u : 0u;
     put_prep(S, d, sl, S.prep, ok);
     S.next = 0;
@@ -1227,21 +1236,34 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   }
   CLK_MARK(S, 6);
   // ---- stage 5: tile -> HBM by n threads, this one the i-th; through the L2,
-  // to where every XCD sees it, if some block copies from this one
+  // to where every XCD sees it, if some block copies from this one.  Four LDS
+  // reads go out together: one at a time, a wave alone took a round trip for
+  // each of its 16 (or, of 8 bytes, 32) stores.
   auto store_tile = [&](uint32_t i, uint32_t n) {
     if (!dst) return;
-    if (used) {
-      uint64_t* d8 = reinterpret_cast<uint64_t*>(dst);
-      const uint64_t* s8 = reinterpret_cast<const uint64_t*>(S.tile);
-      for (uint32_t c = i; c < blen >> 3; c += n)
-        __hip_atomic_store(d8 + c, s8[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (uint32_t c = (blen & ~7u) + i; c < blen; c += n)
-        __hip_atomic_store(dst + c, S.tile[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      const uint4* s4 = reinterpret_cast<const uint4*>(S.tile);
-      uint4* d4 = reinterpret_cast<uint4*>(dst);
-      for (uint32_t c = i; c < blen >> 4; c += n) d4[c] = s4[c];
-      for (uint32_t c = (blen & ~15u) + i; c < blen; c += n) dst[c] = S.tile[c];
+    const uint32_t full = blen >> 4;
+    const u32x4* s4 = reinterpret_cast<const u32x4*>(S.tile);
+    for (uint32_t c = i; c < full; c += 4 * n) {
+      u32x4 v[4] = {};
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++)
+        if (c + u * n < full) v[u] = s4[c + u * n];
+#pragma unroll
+      for (uint32_t u = 0; u < 4; u++) {
+        uint8_t* p = dst + 16 * (uint64_t)(c + u * n);
+        if (c + u * n >= full) break;
+        if (used) {
+          uint64_t* q = reinterpret_cast<uint64_t*>(p);
+          __hip_atomic_store(q, (uint64_t)v[u][0] | ((uint64_t)v[u][1] << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          __hip_atomic_store(q + 1, (uint64_t)v[u][2] | ((uint64_t)v[u][3] << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          *reinterpret_cast<u32x4*>(p) = v[u];
+        }
+      }
+    }
+    for (uint32_t c = 16 * full + i; c < blen; c += n) {
+      if (used) __hip_atomic_store(dst + c, S.tile[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else dst[c] = S.tile[c];
     }
   };
   // No workgroup barrier from here to the end of the passes: wave 0 and
@@ -1382,13 +1404,12 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     __builtin_amdgcn_s_setprio(1);
     CLK_ADD(S, 13, CLK_NOW() - c4_);
   }
-  if (wv == 0 && ov) {
-    // stage 5 by wave 0 alone, while the others prepare the next block
+  if (wv == 0 && ov && used) {
+    // others may be waiting for this block: stage 5 by wave 0 alone, while the
+    // others prepare the next block
     store_tile(lane, 64);
-    if (used) {
-      vm_wait();
-      if (lane == 0) __hip_atomic_store(A.flags + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    vm_wait();
+    if (lane == 0) __hip_atomic_store(A.flags + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else if (wv != 0 && ov) {
     // the preparation has slack (it ends well before wave 0's passes): it
     // yields issue to the waves on their workgroups' critical paths
@@ -1407,7 +1428,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   }
 
   // ---- stage 5, unless wave 0 has done it
-  if (!ov) store_tile(t, kWG);
+  if (!(ov && used)) store_tile(t, kWG);
   CLK_MARK(S, 8);
 #ifdef LZ_STAGE_CLOCKS
   if (t == 0) S.clk[9] += 1;
