@@ -28,6 +28,7 @@
 // No MFMA: nothing here is a contraction.
 #include <hip/hip_runtime.h>
 
+#include <cstddef>
 #include <cstdint>
 
 #include "lz_device.h"
@@ -74,10 +75,22 @@ constexpr uint32_t kDeps = 256;                   // dependencies whose ids are 
 #define CLK_NOW() 0ull
 #endif
 
-// All LDS is static: 53,568 B.  Three workgroups per CU need at most 53,760 B
+// All LDS is static: 53,728 B.  Three workgroups per CU need at most 53,760 B
 // each (LDS is handed out in pieces of 1,280 B, 128 per CU).
 struct Smem {
   uint32_t lut[kLutLit];       // literal decode entries: symbol | f << 8 | (slot - c) << 20
+  // right after the table, so that one index reaches both: an entry's index is
+  // its slot, or kLutLit + 256 wave + place in the ring
+  union {
+    struct {
+      uint32_t ringe[kWaves][256]; // rANS words of the literal stream staged per wave:
+      uint16_t ring[kWaves][256];  // the table entry of a word's slot, and the word
+    };
+    struct {                       // between literal stages:
+      alignas(16) uint8_t prep[kPrepRing];   // the next block's payload prefix (prep_ring)
+      uint32_t dep[kDeps];                   // the blocks it copies from
+    };
+  };
   alignas(16) uint8_t tile[kB + 16];   // output tile (16-byte reads may start at its last
                                // byte); until stage 3 a copy of the payload prefix
   // CMD, MLEN, OFF: the symbols that occur, in order (the k-th one: its first
@@ -95,16 +108,6 @@ struct Smem {
   uint16_t lst[kMaxSeq];       // [0, n_ext): matches from earlier blocks (any order);
                                // [kMaxSeq - n_in, kMaxSeq): in-block matches, last first;
                                // stage 4: dependency range of in-block match a
-  union {
-    struct {
-      uint16_t ring[kWaves][256];  // rANS words of the literal stream staged per wave
-      uint32_t ringe[kWaves][256]; // table entry of each staged word's slot
-    };
-    struct {                       // between literal stages:
-      alignas(16) uint8_t prep[kPrepRing];   // the next block's payload prefix (prep_ring)
-      uint32_t dep[kDeps];                   // the blocks it copies from
-    };
-  };
   union {
     struct {
       uint16_t fdst[64], flen[64], frng[64]; // at most 64 in-block matches: destination,
@@ -126,6 +129,8 @@ struct Smem {
   uint64_t clk[kClkSlots], clk_last;
 #endif
 };
+
+static_assert(offsetof(Smem, ringe) == 4 * kLutLit && kLutLit % 1024 == 0, "one index for table and rings");
 
 struct DevArgs {
   const uint8_t* arc;
@@ -368,6 +373,9 @@ __device__ bool lit_group(const uint8_t* body, uint32_t K, uint32_t n, uint32_t 
   constexpr uint32_t mask = (1u << P) - 1;
   uint16_t* ring = S.ring[wv];
   uint32_t* ringe = S.ringe[wv];
+  const uint32_t* ent = S.lut;
+  const uint32_t first = kLutLit + 256 * wv;           // this wave's ring, as an index of ent
+  const uint16_t* words = &S.ring[0][0] - kLutLit;     // ... and of words
   uint32_t x = L.x;
   bool ok = x >= kL && L.woff + nwg <= nw_total;
   // slices 0 and 1 into the ring, slices 2..5 wait in registers
@@ -419,10 +427,13 @@ __device__ bool lit_group(const uint8_t* body, uint32_t K, uint32_t n, uint32_t 
     }
     const bool need = act && x < kL;
     const uint64_t bal = __ballot(need);
-    const uint32_t q = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                 __builtin_amdgcn_mbcnt_lo((uint32_t)bal, pos)) & 255u;
-    const uint32_t w = ring[q];
-    e = need ? ringe[q] : S.lut[x & mask];
+    const uint32_t q = (__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)bal, pos)) & 255u) | first;
+    const uint32_t w = words[q];
+    // a select made of bits: of two conditions the compiler makes a branch,
+    // and the two reads follow each other
+    const uint32_t sel = 0u - (uint32_t)need;
+    e = ent[((q ^ (x & mask)) & sel) ^ (x & mask)];
     x = need ? (x << 16) | w : x;
     pos += (uint32_t)__popcll(bal);
     // end of the lane's literal run in this sequence: the next sequence
@@ -445,14 +456,12 @@ __device__ bool lit_group(const uint8_t* body, uint32_t K, uint32_t n, uint32_t 
       }
     }
   };
-  // A round that enters slice s0+1 stages slice s0+2 from the registers into
-  // the ring half of slice s0 and loads slice s0+kPreSlices into them. Written
-  // out in this scope: inside the round helper, which takes its state by
-  // reference, the registers would be spilled to a private array.
-#define LZ_ROUND(act)                                                   \
-  {                                                                     \
-    const uint32_t s0 = pos >> 7;                                       \
-    round(act);                                                         \
+  // Two rounds use up at most a slice of 128 words, and two are staged: after
+  // every second round, once slice s0+1 is entered, slice s0+2 goes from the
+  // registers into the ring half of slice s0, and slice s0+kPreSlices is loaded
+  // into them. Written out in this scope: inside the round helper, which takes
+  // its state by reference, the registers would be spilled to a private array.
+#define LZ_STAGE()                                                      \
     if ((pos >> 7) != s0) {                                             \
       __builtin_amdgcn_wave_barrier(); /* every lane read slice s0 */   \
       const uint32_t d = ((s0 & 1) << 7) + lane;                        \
@@ -466,15 +475,21 @@ __device__ bool lit_group(const uint8_t* body, uint32_t K, uint32_t n, uint32_t 
         u0 = ldw(b3 + lane);                                            \
         u1 = ldw(b3 + 64 + lane);                                       \
       }                                                                 \
-    }                                                                   \
+    }
+  const bool on = FULL || lane_ok;
+  for (uint32_t r = 0; r + 1 < R; r += 2) {
+    const uint32_t s0 = pos >> 7;
+    round(on);
+    round(on);
+    LZ_STAGE()
   }
-  if (FULL) {
-    for (uint32_t r = 0; r < R; r++) LZ_ROUND(true)
-  } else {
-    for (uint32_t r = 0; r < R; r++) LZ_ROUND(lane_ok)
+  if (R & 1) {
+    const uint32_t s0 = pos >> 7;
+    round(on);
+    LZ_STAGE()
   }
   if (ex) round(lane_ok && k < ex);     // no read follows: nothing to stage
-#undef LZ_ROUND
+#undef LZ_STAGE
   ok = ok && (!lane_ok || x == kL) && pos == nwg;
   return __ballot(!ok) == 0;
 }
