@@ -874,9 +874,10 @@ __device__ __forceinline__ void tile_copy(Smem& S, uint32_t dst, uint32_t src, u
 // In-block match of M bytes to tile position d0 from s = d0 - d (s < 0: its
 // first bytes lie in earlier blocks), by one wave: the d (or M) bytes before
 // the match repeats itself are copied, then what is there is appended to
-// itself, doubling, until M bytes stand.  A match that fills its block with
-// period 2 takes 14 steps (about 2 us); byte by byte, 64 at a time and each
-// step waiting for the one before, it was 27 us of a block's 55.
+// itself, doubling, until M bytes stand; a period that divides 16 is laid out
+// in a register and stored.  A match that fills its block with period 2 was
+// 27 us of a block's 55 byte by byte, 64 at a time and each step waiting for
+// the one before.
 __device__ __forceinline__ void copy_long(Smem& S, const DevArgs& A, uint64_t sb, uint32_t d0, uint32_t M,
                                           int32_t s, uint32_t d, bool& bad) {
   const uint32_t lane = lane_id();
@@ -895,6 +896,16 @@ __device__ __forceinline__ void copy_long(Smem& S, const DevArgs& A, uint64_t sb
     }
   }
   if (n > n0) tile_copy(S, d0 + n0, (uint32_t)(s + (int32_t)n0), n - n0);
+  if (d < M && d <= 16 && (d & (d - 1)) == 0) {
+    // a period that divides 16: every 16 bytes are the same
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const u32x4 w = ld128(S.tile + d0);
+    const uint32_t x = d == 1 ? (w[0] & 0xFFu) * 0x01010101u : (d == 2 ? (w[0] & 0xFFFFu) * 0x00010001u : w[0]);
+    const uint32_t y = d >= 8 ? w[1] : x;
+    const u32x4 v = {x, y, d == 16 ? w[2] : x, d == 16 ? w[3] : y};
+    for (uint32_t k = 16 * lane; k < M; k += 1024) st_upto16(S.tile + d0 + k, v, min(16u, M - k));
+    return;
+  }
   for (uint32_t f = n; f < M; f += min(f, M - f)) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // reads what was written
     tile_copy(S, d0 + f, d0, min(f, M - f));
@@ -1715,27 +1726,27 @@ int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
 }
 
 // Whole-file decodes of n <= 4 non-empty archives at once, out[k] the output
-// of h[k].  Workgroups are shared out by blocks, at least sixteen an archive
-// (a short one with many levels is a chain that two or three can follow), the
-// deepest archive first: one after the other, the streams of a 64 MiB FASTQ
-// took 51 + 96 + 181 + 104 us, the 181 for 25 blocks in 34 levels.
+// of h[k].  Every archive gets the workgroups that it would have alone, the
+// shortest archive first (a chain of levels, or a few slow blocks, is best
+// begun at once): as many as fit run, and as an archive's end, the next one's
+// take their places, so the chip stays full whatever a block of each costs.  (With the resident workgroups shared out by blocks, the 350 blocks
+// of a 64 MiB FASTQ's id lines, 50 us each, took 300 us on their 65.)  One
+// after the other the four streams took 51 + 91 + 124 + 98 us, 124 for the 25
+// blocks and as many levels of the '+' lines.
 int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, hipStream_t s) {
   Jobs<4> J{};
   uint32_t at[4], m = 0;
-  uint64_t blocks = 0;
   for (uint32_t k = 0; k < n; k++) {
     uint32_t i = m++;
-    for (; i && h[at[i - 1]]->av.n_levels < h[k]->av.n_levels; i--) at[i] = at[i - 1];
+    for (; i && h[at[i - 1]]->av.n_blocks > h[k]->av.n_blocks; i--) at[i] = at[i - 1];
     at[i] = k;
-    blocks += h[k]->av.n_blocks;
   }
   uint32_t wg = 0;
   for (uint32_t k = 0; k < m; k++) {
     const lz_handle* a = h[at[k]];
-    const uint64_t share = decode_slots(a) * a->av.n_blocks / blocks;
     J.a[k] = whole_file(a, out[at[k]]);
     J.a[k].wg0 = wg;
-    J.a[k].nwg = (uint32_t)std::min<uint64_t>(a->av.n_blocks, std::max<uint64_t>(share, 16));
+    J.a[k].nwg = (uint32_t)std::min<uint64_t>(a->av.n_blocks, decode_slots(a));
     wg += J.a[k].nwg;
   }
   for (uint32_t k = m; k < 4; k++) J.a[k].wg0 = wg;      // no workgroups
