@@ -1052,8 +1052,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
       x.d0 = S.out[q] + L;
       x.of = (uint64_t)S.oflo[q] | ((uint64_t)S.ofhi[q] << 32);
     };
-    auto ext_load = [&](uint32_t e, Ext& x) {
-      ext_fields(e, x);
+    auto ext_load = [&](Ext& x) {
       if (x.M >= 16 && sub < x.M) x.v = src16(A, x.of + min(sub, x.M - 16), bad);
       if (64 + sub < x.M) x.w = src16(A, x.of + min(64 + sub, x.M - 16), bad);
     };
@@ -1063,8 +1062,8 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     };
     Ext first;
     first.v = first.w = u32x4{};
-    first.M = first.d0 = 0;
-    if (!wait) ext_load(slot, first);
+    ext_fields(slot, first);
+    if (!wait) ext_load(first);
     // the workgroup's next place; the literal decode hides the ticket's round
     // trip (several microseconds while every workgroup takes them; taken
     // during the preparation, one block further ahead, it held that up)
@@ -1116,20 +1115,13 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
         }
       }
       __syncthreads();
-      ext_load(slot, first);
+      ext_load(first);
     }
     ext_store(first);
-    for (uint32_t e = 64 + slot; __ballot(e < nx); e += 64) {
-      Ext x;
-      x.v = x.w = u32x4{};
-      ext_load(e, x);
-      ext_store(x);
-    }
-    // what is left: matches longer than 128 bytes, four lanes up to 1 KiB, the
-    // whole wave beyond, and matches of less than 16 bytes byte by byte
-    for (uint32_t e = slot; __ballot(e < nx); e += 64) {
-      Ext x;
-      ext_fields(e, x);
+    // what is left of a match: the bytes past 128, by its four lanes up to 1 KiB
+    // and by the whole wave beyond, or a match of less than 16 bytes, byte by byte
+    auto ext_rest = [&](const Ext& x) {
+      if (!__ballot(x.M > 128 || x.M - 1u < 15u)) return;
       const uint32_t mid = x.M <= 1024 ? x.M : 0u;
       for (uint32_t k0 = 128 + sub; __ballot(k0 < mid); k0 += 256) {
         u32x4 v[4] = {};
@@ -1158,6 +1150,13 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
       const uint32_t few = x.M < 16 ? x.M : 0u;
       for (uint32_t k = t & 3; __ballot(k < few); k += 4)
         if (k < few) S.tile[x.d0 + k] = (uint8_t)src_byte(A, x.of + k, bad);
+    };
+    ext_rest(first);
+    for (uint32_t e = 64 + slot; __ballot(e < nx); e += 64) {
+      ext_fields(e, first);
+      ext_load(first);
+      ext_store(first);
+      ext_rest(first);
     }
     if (bad) S.err = 1;
     if (t == 64) {
