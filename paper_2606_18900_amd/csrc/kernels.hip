@@ -1030,6 +1030,37 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   const bool wait = uni(S.wait) != 0;
   CLK_MARK(S, 3);
 
+  // With at most 64 in-block matches: the earlier ones [nlo, nhi) that lane a's
+  // match copies from (wave 0; stage 4a), worked out while a block waits for
+  // others, or else in stage 4.
+  const uint32_t cnt = min(S.nin, ns);
+  uint32_t nlo = 0, nhi = 0;
+  auto near_ranges = [&]() {
+    // the matches that end at or before the window's start, and those that
+    // start before its end: both arrays ascend, so eight of the 64 entries
+    // name the group of eight that the bound lies in
+    const bool have = lane < cnt;
+    const uint32_t a = have ? lane : 0u, pk = S.fpk[a], dst = S.fdst[a], len = S.flen[a], d = (pk >> 16) & 0x7FFFu;
+    const int32_t s = (int32_t)(pk & 0xFFFFu) - 16384, we = s + (int32_t)min(d, len);
+    const uint32_t beg = have ? dst : 0xFFFFu, end = have ? dst + len : 0xFFFFu;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    S.fdst[lane] = (uint16_t)beg;
+    S.frng[lane] = (uint16_t)end;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    auto below = [&](uint32_t mine, const uint16_t* all, uint32_t x) {    // entries below x
+      uint32_t g = 0;
+#pragma unroll
+      for (uint32_t k = 0; k < 8; k++) g += __builtin_amdgcn_readlane(mine, 8 * k + 7) < x ? 1u : 0u;
+      const u32x4 v = ld128(reinterpret_cast<const uint8_t*>(all + 8 * min(g, 7u)));
+      uint32_t n = 8 * min(g, 7u);
+#pragma unroll
+      for (uint32_t k = 0; k < 4; k++) n += ((v[k] & 0xFFFFu) < x ? 1u : 0u) + ((v[k] >> 16) < x ? 1u : 0u);
+      return n;
+    };
+    nlo = min(below(end, S.frng, (uint32_t)max(s, 0) + 1), 63u);
+    nhi = min(below(beg, S.fdst, (uint32_t)max(we, 0)), 63u);
+  };
+
   // ---- stage 3: literals straight to their tile positions; external matches
   {
     bool bad = false;
@@ -1096,6 +1127,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     CLK_MARK(S, 4);
     if (t == 64 && nit < total) nbq = A.queue[qb + nit];
     if (wait) {
+      if (wv == 0 && cnt && cnt <= 64) near_ranges();
       // The blocks b copies from have smaller tickets, so their workgroups
       // run or have finished, and none of them waits for this one.
       if (64 * wv < nd) {
@@ -1190,7 +1222,6 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   // sequence tables are free, and waves 1..3 prepare the next block
   // meanwhile.  With more, the fields are packed into the sequence tables and
   // 4a uses every thread.
-  const uint32_t cnt = min(S.nin, ns);
   const bool small = cnt <= 64;
   uint16_t* Fd = small ? S.fdst : S.lit;     // destination
   uint16_t* Fl = small ? S.flen : S.out;     // length
@@ -1332,27 +1363,9 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
       const uint32_t d = (pk >> 16) & 0x7FFFu;
       uint32_t plo, phi;                      // the earlier matches of the chunk it copies from
       if (small) {
-        // the matches that end at or before the window's start, and those that
-        // start before its end: both arrays ascend, so eight of the 64 entries
-        // name the group of eight that the bound lies in
-        const uint32_t beg = have ? dst : 0xFFFFu, end = have ? dst + len : 0xFFFFu;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        S.fdst[lane] = (uint16_t)beg;
-        S.frng[lane] = (uint16_t)end;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        auto below = [&](uint32_t mine, const uint16_t* all, uint32_t x) {    // entries below x
-          uint32_t g = 0;
-#pragma unroll
-          for (uint32_t k = 0; k < 8; k++) g += __builtin_amdgcn_readlane(mine, 8 * k + 7) < x ? 1u : 0u;
-          const u32x4 v = ld128(reinterpret_cast<const uint8_t*>(all + 8 * min(g, 7u)));
-          uint32_t n = 8 * min(g, 7u);
-#pragma unroll
-          for (uint32_t k = 0; k < 4; k++) n += ((v[k] & 0xFFFFu) < x ? 1u : 0u) + ((v[k] >> 16) < x ? 1u : 0u);
-          return n;
-        };
-        const int32_t we = s + (int32_t)min(d, len);
-        plo = min(below(end, S.frng, (uint32_t)max(s, 0) + 1), 63u);
-        phi = min(below(beg, S.fdst, (uint32_t)max(we, 0)), 63u);
+        if (!wait) near_ranges();
+        plo = nlo;
+        phi = nhi;
       } else {
         const uint32_t rng = Fr[aa];
         plo = rng & 63u;
