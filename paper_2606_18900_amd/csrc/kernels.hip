@@ -1779,12 +1779,12 @@ int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, 
 // the segment from a start with bit k zero gives the bit the segment xors into
 // bit k, and a prefix xor over the segments (a ballot) gives bit k at every
 // start.  Eight passes of two instructions a byte (two half segments in one
-// packed 16-bit register) replace the chain; the ninth pass is FNV itself, in
-// every segment from its own low byte.
-// 128 MiB in 8192 blocks, blocks and hash over the hashes together: 111 us;
+// packed 16-bit register) replace the chain; a ninth gives the d, summed up
+// with their weights by dot products.
+// 128 MiB in 8192 blocks, blocks and hash over the hashes together: 85 us (63 and 25);
 // with the chain in one thread per block (292 us) and one thread for the hash
-// over the hashes (1353 us) it was 1716 us.  Bound by the instructions of the
-// nine passes, not by memory (27 us at a copy's rate).
+// over the hashes (1353 us) it was 1716 us.  Bound by the passes'
+// instructions, not by memory (27 us at a copy's rate).
 namespace {
 
 constexpr uint32_t kSeg = 64;                    // bytes of a lane's segment
@@ -1798,7 +1798,7 @@ constexpr uint64_t fnv_pow(uint32_t n) {
 }
 __device__ __forceinline__ uint64_t fnv_pow_at(uint32_t n) {      // n <= kChunk
   uint64_t r = 1, q = kFnvPrime;
-#pragma unroll
+#pragma unroll 1
   for (uint32_t s = 0; s < 13; s++) {
     r = n & (1u << s) ? r * q : r;
     q *= q;
@@ -1807,95 +1807,166 @@ __device__ __forceinline__ uint64_t fnv_pow_at(uint32_t n) {      // n <= kChunk
 }
 
 typedef uint16_t u16x2 __attribute__((vector_size(4)));
+typedef int16_t s16x2 __attribute__((vector_size(4)));
+
+// A full segment's sum: bytes i and 32 + i (i < 32) contribute their d with the
+// weights p^(64 - i) and p^(32 - i).  The weights are split into four signed
+// 16-bit digits, so that two-element dot products add both: a digit's sum
+// stays below 64 * 255 * 2^15 < 2^31.
+struct FnvWeights {
+  uint32_t w[4][kSeg / 2];         // digit k of both weights, packed
+};
+constexpr FnvWeights fnv_weights() {
+  FnvWeights f = {};
+  for (uint32_t i = 0; i < kSeg / 2; i++)
+    for (uint32_t h = 0; h < 2; h++) {
+      uint64_t v = fnv_pow(kSeg - kSeg / 2 * h - i);
+      for (uint32_t k = 0; k < 4; k++) {
+        f.w[k][i] |= (uint32_t)(v & 0xFFFFu) << (16 * h);
+        v = (v >> 16) + ((v >> 15) & 1u);        // the digit was taken as signed
+      }
+    }
+  return f;
+}
+
+// Bit k of the low byte at the halves' starts (sa, sb), from the bits xa, xb
+// that the halves xor into it and the bit c before the round; c becomes the
+// bit after it.
+template <uint32_t NW>
+__device__ __forceinline__ void fnv_bit(uint32_t k, uint32_t xa, uint32_t xb, uint32_t& c, uint32_t& sa, uint32_t& sb,
+                                        uint32_t wv, uint32_t (*bits)[8]) {
+  const uint64_t x = __ballot(xa ^ xb);
+  uint32_t all = (uint32_t)__popcll(x), before = c;
+  if (NW > 1) {
+    if (lane_id() == 0) bits[wv][k] = all & 1u;
+    __syncthreads();
+    all = 0;
+    for (uint32_t q = 0; q < NW; q++) {
+      const uint32_t b = bits[q][k];
+      all ^= b;
+      before ^= q < wv ? b : 0u;
+    }
+  }
+  const uint32_t ka = (mbcnt(x) ^ before) & 1u;
+  sa |= ka << k;
+  sb |= (ka ^ xa) << k;
+  c = (c ^ all) & 1u;
+}
+
+// The sum that this lane's segment contributes at its end: the 64 bytes at p
+// or, with PART, only the last m of them (0: p is not read).  low: the low byte
+// of the hash before the round, then after it.
+template <uint32_t NW, bool PART>
+__device__ __forceinline__ uint64_t fnv_segment(const uint8_t* p, uint32_t m, uint32_t& low, uint32_t wv,
+                                                uint32_t (*bits)[8]) {
+  constexpr FnvWeights kW = fnv_weights();
+  uint32_t w[kSeg / 4] = {};
+  if (!PART || m) {
+#pragma unroll
+    for (uint32_t q = 0; q < kSeg / 16; q++) {
+      const u32x4 v = ld128(p + 16 * q);
+#pragma unroll
+      for (uint32_t r = 0; r < 4; r++) w[4 * q + r] = v[r];
+    }
+  }
+  // byte i of the first half segment with byte i of the second
+  u16x2 pr[kSeg / 2], on[kSeg / 2];
+#pragma unroll
+  for (uint32_t i = 0; i < kSeg / 2; i++) {
+    pr[i] = (u16x2){(uint16_t)((w[i / 4] >> (8 * (i % 4))) & 0xFFu),
+                    (uint16_t)((w[kSeg / 8 + i / 4] >> (8 * (i % 4))) & 0xFFu)};
+    on[i] = (u16x2){(uint16_t)(i + m >= kSeg ? 0xFFFFu : 0u), (uint16_t)(i + m >= kSeg / 2 ? 0xFFFFu : 0u)};
+  }
+  uint32_t sa = 0, sb = 0, next = 0;
+#pragma unroll 1
+  for (uint32_t k = 0; k < 8; k++) {
+    u16x2 l = {(uint16_t)sa, (uint16_t)sb};
+#pragma unroll
+    for (uint32_t i = 0; i < kSeg / 2; i++) {
+      const u16x2 x = (l ^ pr[i]) * (uint16_t)0xb3;
+      l = PART ? (x & on[i]) | (l & ~on[i]) : x;
+    }
+    uint32_t c = (low >> k) & 1u;
+    fnv_bit<NW>(k, ((uint32_t)l[0] >> k) & 1u, ((uint32_t)l[1] >> k) & 1u, c, sa, sb, wv, bits);
+    next |= c << k;
+  }
+  low = next;
+  // d = (l ^ byte) - l (the bits of l above its low byte cancel)
+  u16x2 l = {(uint16_t)sa, (uint16_t)sb};
+  int32_t acc[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (uint32_t i = 0; i < kSeg / 2; i++) {
+    const u16x2 x = l ^ pr[i];
+    u16x2 d = x - l;
+    const u16x2 y = x * (uint16_t)0xb3;
+    if (PART) d = d & on[i];
+    l = PART ? (y & on[i]) | (l & ~on[i]) : y;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; k++) {
+      const s16x2 c = {(int16_t)(kW.w[k][i] & 0xFFFFu), (int16_t)(kW.w[k][i] >> 16)};
+      acc[k] = __builtin_amdgcn_sdot2((s16x2)d, c, acc[k], false);
+    }
+  }
+  return (uint64_t)(int64_t)acc[0] + ((uint64_t)(int64_t)acc[1] << 16) + ((uint64_t)(int64_t)acc[2] << 32) +
+         ((uint64_t)(int64_t)acc[3] << 48);
+}
 
 // A workgroup of NW waves extends the hash h by the n bytes at p, kChunk * NW
 // bytes a round (NW = 1: each wave on its own bytes, no barrier).  Every lane
-// returns the hash.
+// returns the hash.  Whole rounds only carry the low byte from one to the
+// next: each lane's sums are weighted and added up over the rounds, and the
+// lanes put together once at the end.  The last, shorter round takes whole
+// segments and one segment whose last m bytes are the data's (its window
+// begins in the segment before).
 template <uint32_t NW>
 __device__ uint64_t fnv_extend(uint64_t h, const uint8_t* p, uint64_t n, uint64_t (*part)[2], uint32_t (*bits)[8]) {
+  if (n < kSeg) {
+    for (uint64_t i = 0; i < n; i++) h = (h ^ p[i]) * kFnvPrime;
+    return h;
+  }
   const uint32_t lane = lane_id(), wv = NW > 1 ? uni(threadIdx.x >> 6) : 0u;
-  for (uint64_t at = 0; at < n; at += (uint64_t)kChunk * NW) {
-    const uint32_t todo = (uint32_t)min((uint64_t)kChunk * NW, n - at);
-    const uint32_t o = wv * kChunk + lane * kSeg;                 // this lane's segment
-    const uint32_t m = o < todo ? min(kSeg, todo - o) : 0u;
-    const bool full = uni(todo == kChunk * NW);
-    uint32_t w[kSeg / 4];
-    if (m == kSeg) {
+  const uint32_t o = wv * kChunk + lane * kSeg;                   // this lane's segment
+  uint64_t at = 0, T = 0;
+  uint32_t low = (uint32_t)h & 0xFFu;
+  for (; at + kChunk * NW <= n; at += kChunk * NW) {
+    T = T * fnv_pow(kChunk * NW) + fnv_segment<NW, false>(p + at + o, kSeg, low, wv, bits);
+    h *= fnv_pow(kChunk * NW);
+  }
+  if (at) {
 #pragma unroll
-      for (uint32_t q = 0; q < kSeg / 16; q++) {
-        const u32x4 v = ld128(p + at + o + 16 * q);
-#pragma unroll
-        for (uint32_t r = 0; r < 4; r++) w[4 * q + r] = v[r];
-      }
-    } else {
-#pragma unroll
-      for (uint32_t q = 0; q < kSeg / 4; q++) {
-        w[q] = 0;
-        for (uint32_t r = 0; r < 4; r++)
-          if (4 * q + r < m) w[q] |= (uint32_t)p[at + o + 4 * q + r] << (8 * r);
-      }
+    for (uint32_t s = 0; s < 6; s++) {                            // lane 0: the wave's sum
+      const uint64_t right = __shfl(T, (int)(lane + (1u << s)) & 63);
+      T = T * fnv_pow(kSeg << s) + right;
     }
-    // byte i of the first half segment with byte i of the second
-    u16x2 pr[kSeg / 2];
-#pragma unroll
-    for (uint32_t i = 0; i < kSeg / 2; i++)
-      pr[i] = (u16x2){(uint16_t)((w[i / 4] >> (8 * (i % 4))) & 0xFFu),
-                      (uint16_t)((w[kSeg / 8 + i / 4] >> (8 * (i % 4))) & 0xFFu)};
-    uint32_t sa = 0, sb = 0;                                      // low byte at the halves' starts
-#pragma unroll 1
-    for (uint32_t k = 0; k < 8; k++) {
-      u16x2 l = {(uint16_t)sa, (uint16_t)sb};
-      if (full) {
-#pragma unroll
-        for (uint32_t i = 0; i < kSeg / 2; i++) l = (l ^ pr[i]) * (uint16_t)0xb3;
-      } else {
-#pragma unroll
-        for (uint32_t i = 0; i < kSeg / 2; i++) {
-          const u16x2 x = (l ^ pr[i]) * (uint16_t)0xb3;
-          l[0] = i < m ? x[0] : l[0];
-          l[1] = i + kSeg / 2 < m ? x[1] : l[1];
-        }
-      }
-      const uint32_t xa = ((uint32_t)l[0] >> k) & 1u, xb = ((uint32_t)l[1] >> k) & 1u;
-      const uint64_t x = __ballot(xa ^ xb);
-      uint32_t c = (uint32_t)(h >> k) & 1u;                       // bit k before this round
-      if (NW > 1) {
-        if (lane == 0) bits[wv][k] = (uint32_t)__popcll(x) & 1u;
-        __syncthreads();
-        for (uint32_t q = 0; q < wv; q++) c ^= bits[q][k];
-      }
-      const uint32_t ka = (mbcnt(x) ^ c) & 1u;
-      sa |= ka << k;
-      sb |= (ka ^ xa) << k;
-    }
-    // T: what the segment adds to the hash at its end
-    uint64_t f = sa;
-#pragma unroll
-    for (uint32_t i = 0; i < kSeg; i++) {
-      const uint64_t g = (f ^ ((w[i / 4] >> (8 * (i % 4))) & 0xFFu)) * kFnvPrime;
-      f = full || i < m ? g : f;
-    }
-    uint64_t T;
-    if (full) {
-      T = f - sa * fnv_pow(kSeg);
-#pragma unroll
-      for (uint32_t s = 0; s < 6; s++) {                          // lane 0: the wave's sum
-        const uint64_t right = __shfl(T, (int)(lane + (1u << s)) & 63);
-        T = T * fnv_pow(kSeg << s) + right;
-      }
-    } else {
-      T = (f - sa * fnv_pow_at(m)) * fnv_pow_at(min(kChunk, o + m < todo ? min(todo, (wv + 1) * kChunk) - o - m : 0u));
-      for (uint32_t s = 32; s; s >>= 1) T += __shfl(T, (int)(lane + s) & 63);
-    }
-    const uint32_t len = wv * kChunk < todo ? min(kChunk, todo - wv * kChunk) : 0u;
     if (NW == 1) {
-      h = h * (full ? fnv_pow(kChunk) : fnv_pow_at(len)) + __shfl(T, 0);
+      h += __shfl(T, 0);
+    } else {
+      if (lane == 0) part[wv][0] = T;
+      __syncthreads();
+      uint64_t sum = 0;
+#pragma unroll 1
+      for (uint32_t q = 0; q < NW; q++) sum = sum * fnv_pow(kChunk) + part[q][0];
+      h += sum;
+      __syncthreads();
+    }
+  }
+  if (at < n) {                                                   // the rest, less than a round
+    const uint32_t todo = (uint32_t)(n - at);
+    const uint32_t m = o < todo ? min(kSeg, todo - o) : 0u;
+    const uint32_t end = min(todo, (wv + 1) * kChunk);            // of the wave's bytes
+    uint64_t R = fnv_segment<NW, true>(p + at + o + m - kSeg, m, low, wv, bits);
+    R *= fnv_pow_at(o + m < end ? end - o - m : 0u);
+    for (uint32_t s = 32; s; s >>= 1) R += __shfl(R, (int)(lane + s) & 63);
+    const uint32_t len = wv * kChunk < todo ? end - wv * kChunk : 0u;
+    if (NW == 1) {
+      h = h * fnv_pow_at(len) + __shfl(R, 0);
     } else {
       if (lane == 0) {
-        part[wv][0] = T;
-        part[wv][1] = full ? fnv_pow(kChunk) : fnv_pow_at(len);
+        part[wv][0] = R;
+        part[wv][1] = fnv_pow_at(len);
       }
       __syncthreads();
+#pragma unroll 1
       for (uint32_t q = 0; q < NW; q++) h = h * part[q][1] + part[q][0];
       __syncthreads();
     }

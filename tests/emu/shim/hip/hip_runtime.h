@@ -121,6 +121,8 @@ inline uint32_t __builtin_amdgcn_alignbyte(uint32_t hi, uint32_t lo, uint32_t s)
   return (uint32_t)((((uint64_t)hi << 32) | lo) >> (8 * (s & 3)));
 }
 inline void __builtin_amdgcn_s_sleep(int) { }
+typedef int16_t emu_s16x2 __attribute__((vector_size(4)));
+inline int __builtin_amdgcn_sdot2(emu_s16x2 a, emu_s16x2 b, int c, bool) { return c + a[0] * b[0] + a[1] * b[1]; }
 inline uint32_t __umul24(uint32_t a, uint32_t b) { return (a & 0xFFFFFFu) * (b & 0xFFFFFFu); }
 inline int __popcll(unsigned long long v) { return __builtin_popcountll(v); }
 
