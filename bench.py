@@ -25,14 +25,13 @@ FASTQ_PARAMS = dict(kind=1, block_log2=14, max_level=64, min_match=16, hash_len=
                     seq_lanes=64, prob_bits=(12, 10, 10, 10), level_penalty=32)
 HBM_PEAK_GBPS = 8000.0      # MI355X HBM3E
 
-# HBM bytes moved by one whole-file decode of the 1 GiB archive (per-level
-# launches), from two rocprofv3 --pmc runs of `bench.py --legs decode`
-# (FETCH_SIZE, then WRITE_SIZE, summed over the k_decode dispatches of a
-# decode), each scaled by what the same counter reads for a 1 GiB device copy
+# HBM bytes moved by one whole-file decode of the 1 GiB archive (one launch),
+# from two rocprofv3 --pmc runs of `bench.py --legs decode` (FETCH_SIZE, then
+# WRITE_SIZE, of the k_decode dispatch), each scaled by what the same counter reads for a 1 GiB device copy
 # (`bench.py --legs copy`: FETCH_SIZE x 1.99995, WRITE_SIZE x 1.0).  Reported
 # only while the decoder source is the one the counters were taken on.
-PMC_TRAFFIC = {"kernels_sha256_16": "bd7fcdca2841bb4d", "bytes": 1 << 30,
-               "fetch": 603599826, "write": 1073741536}
+PMC_TRAFFIC = {"kernels_sha256_16": "7a5ae016bd0167a0", "bytes": 1 << 30,
+               "fetch": 618944910, "write": 1345668448}
 
 
 def log(msg: str) -> None:
@@ -99,8 +98,8 @@ def batched_lookups_leg(arc, starts, N, dev, log, src):
     batches through one captured HIP graph per batch size; each batch is
     copied in, replayed and waited for.  Batch size 1 without a graph is the
     one-launch-sequence-per-request baseline (run on the first 4096 requests);
-    batches of 256 and 4096 are also run with the closure decoded by one
-    cooperative launch (eager)."""
+    batches of 256 and 4096 are also run with one launch per level of
+    the closure (eager)."""
     import numpy as np
     import torch
     from gen.requests import batched_lookups
@@ -109,13 +108,12 @@ def batched_lookups_leg(arc, starts, N, dev, log, src):
     rec = np.diff(starts)
     nbytes = np.where(kind == 0, rec[np.minimum(a, len(rec) - 1)], b)
     res = {}
-    # (batch size, graph, requests, closure decode mode): per-level launches
-    # captured in graphs, and one cooperative launch per batch (eager: a
-    # cooperative launch is not captured)
-    for bs, use_graph, limit, persist in ((1, False, 4096, 0), (1, True, 4096, 0), (16, True, 1 << 16, 0),
+    # (batch size, graph, requests, closure decode mode): one decode launch a
+    # batch captured in graphs, and one launch per level (eager)
+    for bs, use_graph, limit, levels in ((1, False, 4096, 0), (1, True, 4096, 0), (16, True, 1 << 16, 0),
                                           (256, True, 1 << 20, 0), (4096, True, 1 << 20, 0),
                                           (256, False, 1 << 18, 1), (4096, False, 1 << 20, 1)):
-        arc.set_tuning(req_sync_mode=persist)
+        arc.set_tuning(req_sync_mode=levels)
         n_req = min(limit, len(kind))
         nb = n_req // bs
         cap = int(max(nbytes[q * bs:(q + 1) * bs].sum() for q in range(nb)))
@@ -135,7 +133,7 @@ def batched_lookups_leg(arc, starts, N, dev, log, src):
             o = int(starts[a[r]]) if kind[r] == 0 else int(a[r])
             if got[j] != src[o:o + int(nbytes[r])]:
                 raise RuntimeError("batched lookup mismatch (batch size %d, request %d)" % (bs, r))
-        key = "batch%d%s" % (bs, "_persistent" if persist else ("" if use_graph else "_eager"))
+        key = "batch%d%s" % (bs, "_per_level" if levels else ("" if use_graph else "_eager"))
         res[key] = {"requests": nb * bs, "req_per_s": round(nb * bs / wall, 1),
                     "GB_per_s": round(float(nbytes[:nb * bs].sum()) / wall / 1e9, 3),
                     "batch_p50_us": pct(lat, 50), "batch_p99_us": pct(lat, 99)}
@@ -217,7 +215,7 @@ def genome_leg(args) -> int:
                                  "decompressed_bytes": N, "archive_bytes": len(a),
                                  "window_bytes": win, "windows": -(-N // win),
                                  "blocks": arc.n_blocks, "levels": int(arc.info.n_levels),
-                                 "launch": "per-level" if best[0] == 0 else "persistent"}}), flush=True)
+                                 "launch": "one" if best[0] == 0 else "per-level"}}), flush=True)
     return 0
 
 
@@ -408,7 +406,7 @@ def deep_leg(x: bytes, starts, args, dev, threads: int, steps: int = 10) -> dict
     res = {"bytes": N, "levels": int(arc.info.n_levels), "blocks": int(arc.info.n_blocks),
            "ratio": round(N / len(a), 4), "encode_s": round(enc_s, 1),
            "what": "first 256 MiB of the FASTQ, level penalty 0 (levels up to the cap of 64)"}
-    for mode, name in ((0, "per_level_gbps"), (1, "persistent_gbps")):
+    for mode, name in ((0, "one_launch_gbps"), (1, "per_level_gbps")):
         arc.set_tuning(sync_mode=mode, wg_per_cu=3)
         out.zero_()
         arc.decode_all(out)
@@ -431,8 +429,8 @@ def deep_leg(x: bytes, starts, args, dev, threads: int, steps: int = 10) -> dict
         arc.sync_status()
         ms = float(np.mean([e0.elapsed_time(e1) for e0, e1 in evs]))
         res[name] = round(N / (ms / 1e3) / 1e9, 1)
-    log("deep FASTQ (beta 0): %d levels, ratio %.3f; per-level launches %.1f GB/s, persistent %.1f GB/s"
-        % (res["levels"], res["ratio"], res["per_level_gbps"], res["persistent_gbps"]))
+    log("deep FASTQ (beta 0): %d levels, ratio %.3f; one launch %.1f GB/s, per-level launches %.1f GB/s"
+        % (res["levels"], res["ratio"], res["one_launch_gbps"], res["per_level_gbps"]))
     return res
 
 
@@ -591,7 +589,7 @@ STAGES = ["payload copy", "stream headers", "short streams (CMD, MLEN, OFF)",
 
 def stage_clocks(arc, out) -> int:
     """Cycles per block of each decode-kernel stage, summed over all
-    workgroups of one whole-file decode (per-level launches) by the
+    workgroups of one whole-file decode (one launch) by the
     instrumented build; printed as a table on stderr."""
     import torch
     ctl_off = int(arc.info.workspace_bytes) - 512          # control words: last section
@@ -752,11 +750,11 @@ def main() -> int:
         arc.set_tuning(sync_mode=0, wg_per_cu=3)
         print(json.dumps({"read_access_us": read_latency(arc, starts, 200, dev)}), flush=True)
         return 0
-    # both launch modes: one launch per dependency level, and one cooperative
-    # launch whose workgroups walk the levels with a grid barrier between them
+    # both launch modes: one launch whose workgroups wait for the blocks they
+    # copy from, and one launch per dependency level
     modes = {}
-    for mode, name in (((0, "per-level launches"),) if args.legs == "decode" else
-                       ((0, "per-level launches"), (1, "persistent"))):
+    for mode, name in (((0, "one launch"),) if args.legs == "decode" else
+                       ((0, "one launch"), (1, "per-level launches"))):
         wall, ms = run(mode, 3, args.steps, args.warmup)
         modes[mode] = (wall, ms)
         log("%s: %.3f ms/decode (events), %.1f GB/s" % (name, np.mean(ms), N / (np.mean(ms) / 1e3) / 1e9))
@@ -766,8 +764,8 @@ def main() -> int:
     ms_step = wall * 1e3 / args.steps
     value = N * args.steps / wall / 1e9
     kern_ms = float(np.mean(ms))
-    launch = ("one launch per dependency level, 3 workgroups/CU" if best == 0
-              else "persistent, 3 workgroups/CU, grid barrier per level")
+    launch = ("one launch, 3 workgroups/CU, blocks by ticket" if best == 0
+              else "one launch per dependency level, 3 workgroups/CU")
     log("reported: %s, %.3f ms/step wall, %.1f GB/s" % (launch, ms_step, value))
     arc.set_tuning(sync_mode=best, wg_per_cu=3)
 

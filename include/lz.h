@@ -93,11 +93,13 @@ typedef struct lz_request {
 
 /* Launch knobs (chosen by the autotuner; none of them changes a decoded byte). */
 typedef struct lz_tuning {
-  uint32_t sync_mode;   /* whole-file decode: 0 = one launch per dependency
-                           level (lz_open's default), 1 = one cooperative
-                           launch with a grid barrier between levels      */
-  uint32_t wg_per_cu;   /* grid = wg_per_cu * CUs workgroups (a level launch
-                           takes at most its block count); 1..4, default 3   */
+  uint32_t sync_mode;   /* whole-file decode: 0 = one launch whose workgroups
+                           take the blocks in level order and wait for the
+                           completion flags of the blocks they copy from
+                           (lz_open's default), 1 = one launch per
+                           dependency level                               */
+  uint32_t wg_per_cu;   /* grid = wg_per_cu * CUs workgroups (a launch takes at
+                           most its block count); 1..4, default 3            */
   uint32_t spin_limit;  /* watchdog: max polls of a dependency flag before the
                            kernel gives up with LZ_ECORRUPT (0 = default)     */
   uint32_t req_sync_mode; /* request calls (ranges, reads, batches): the same

@@ -24,7 +24,8 @@
 // Background section).  One launch decodes them all: a workgroup takes its
 // blocks by ticket, does everything of a block that needs no other block, and
 // waits for the completion flags of the blocks it copies from only before
-// those copies.  (One launch per level is the other mode.)
+// those copies.  (Static slices, of one level or of each level in a launch of
+// its own, are the other mode.)
 // No MFMA: nothing here is a contraction.
 #include <hip/hip_runtime.h>
 
@@ -1537,15 +1538,15 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
 // (256 MiB FASTQ 826 us, against 583 us with a launch per level).  So a tile
 // is stored through the L2 (agent-scope stores) and its flag only after every
 // wave's stores have completed (both only if some block copies from it: of a
-// FASTQ a third of the blocks, of a genome a tenth); and a reader cannot hold an old copy of a
-// line, as caches start a kernel without one and no line of a block is read
-// before its flag is seen -- unless blocks share lines, because the output is
+// FASTQ a third of the blocks, of a genome a tenth); and a reader cannot hold
+// an old copy of a line, as caches start a kernel without one and no line of a
+// block is read before its flag is seen -- unless blocks share lines, because the output is
 // not aligned to them (A.flow 2): then sources are read by agent-scope loads.
 // (Tickets of two or four consecutive blocks, to take fewer, delay the blocks
 // that others wait for: 64 levels 1134 us instead of 600.)
 // A launch per level costs at least a block's latency (28 us) a level:
-// 256 MiB FASTQ (6 levels) 583 us so and 500 us by ticket, 128 MiB genome (7)
-// 432 and 306, 64 MiB FASTQ of 64 levels 1763 and 595, one record 135 and 64.
+// 256 MiB FASTQ (6 levels) 497 us so and 445 us by ticket, 128 MiB genome (7)
+// 468 and 288, 64 MiB FASTQ of 64 levels 1513 and 394.
 // Otherwise a grid-stride slice of the queue's blocks q_begin .. q_end (one
 // level).
 // Jobs: up to four archives in one launch (the streams of a split container).
@@ -1754,9 +1755,10 @@ int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
 // of h[k].  Every archive gets the workgroups that it would have alone, the
 // shortest archive first (a chain of levels, or a few slow blocks, is best
 // begun at once): as many as fit run, and as an archive's end, the next one's
-// take their places, so the chip stays full whatever a block of each costs.  (With the resident workgroups shared out by blocks, the 350 blocks
-// of a 64 MiB FASTQ's id lines, 50 us each, took 300 us on their 65.)  One
-// after the other the four streams took 51 + 91 + 124 + 98 us, 124 for the 25
+// take their places, so the chip stays full whatever a block of each costs.
+// (With the resident workgroups shared out by blocks, the 350 blocks of a
+// 64 MiB FASTQ's id lines, 50 us each, took 300 us on their 65.)  One after
+// the other the four streams took 51 + 91 + 124 + 98 us, 124 for the 25
 // blocks and as many levels of the '+' lines.
 int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, hipStream_t s) {
   Jobs<4> J{};

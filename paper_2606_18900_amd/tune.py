@@ -2,8 +2,8 @@
 counts of an encoding.
 
 Whole-file decode (`tune`): the decode kernel's synchronisation mode (one
-launch per dependency level, or one cooperative launch with a grid barrier
-between levels) and the workgroups per CU of its grid (1..3: the kernel's
+launch whose workgroups wait for the blocks they copy from, or one launch per
+dependency level) and the workgroups per CU of its grid (1..3: the kernel's
 launch bounds and its 52 KB of LDS hold three workgroups per CU, so more only
 queue).  Every candidate decodes the archive into the same buffer and must
 reproduce the archive's source FNV tree (device hash of the output), so a
