@@ -1793,10 +1793,11 @@ int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, 
 // lowest: with the bits below k known at every segment's start, a pass over
 // the segment from a start with bit k zero gives the bit the segment xors into
 // bit k, and a prefix xor over the segments (a ballot) gives bit k at every
-// start.  Eight passes of two instructions a byte (two half segments in one
-// packed 16-bit register) replace the chain; a ninth gives the d, summed up
+// start.  Bit 0 is the parity of the bytes' bits 0; seven passes of one
+// instruction a byte (two a pair, two half segments in one packed 16-bit
+// register) replace the rest of the chain, and one more gives the d, summed up
 // with their weights by dot products.
-// 128 MiB in 8192 blocks, blocks and hash over the hashes together: 85 us (63 and 25);
+// 128 MiB in 8192 blocks, blocks and hash over the hashes together: 80 us (58 and 25);
 // with the chain in one thread per block (292 us) and one thread for the hash
 // over the hashes (1353 us) it was 1716 us.  Bound by the passes'
 // instructions, not by memory (27 us at a copy's rate).
@@ -1888,13 +1889,22 @@ __device__ __forceinline__ uint64_t fnv_segment(const uint8_t* p, uint32_t m, ui
   u16x2 pr[kSeg / 2], on[kSeg / 2];
 #pragma unroll
   for (uint32_t i = 0; i < kSeg / 2; i++) {
-    pr[i] = (u16x2){(uint16_t)((w[i / 4] >> (8 * (i % 4))) & 0xFFu),
-                    (uint16_t)((w[kSeg / 8 + i / 4] >> (8 * (i % 4))) & 0xFFu)};
+    pr[i] = (u16x2)__builtin_amdgcn_perm(w[kSeg / 8 + i / 4], w[i / 4], 0x0C040C00u + 0x00010001u * (i % 4));
     on[i] = (u16x2){(uint16_t)(i + m >= kSeg ? 0xFFFFu : 0u), (uint16_t)(i + m >= kSeg / 2 ? 0xFFFFu : 0u)};
   }
   uint32_t sa = 0, sb = 0, next = 0;
+  if (!PART) {                                   // bit 0: the parity of the bytes' bits 0
+    uint32_t xa = 0, xb = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < kSeg / 8; q++) {
+      xa ^= w[q];
+      xb ^= w[kSeg / 8 + q];
+    }
+    next = low & 1u;
+    fnv_bit<NW>(0, __builtin_popcount(xa & 0x01010101u) & 1u, __builtin_popcount(xb & 0x01010101u) & 1u, next, sa, sb, wv, bits);
+  }
 #pragma unroll 1
-  for (uint32_t k = 0; k < 8; k++) {
+  for (uint32_t k = PART ? 0 : 1; k < 8; k++) {
     u16x2 l = {(uint16_t)sa, (uint16_t)sb};
 #pragma unroll
     for (uint32_t i = 0; i < kSeg / 2; i++) {

@@ -120,6 +120,15 @@ inline uint32_t __builtin_amdgcn_mbcnt_hi(uint32_t m, uint32_t base) {
 inline uint32_t __builtin_amdgcn_alignbyte(uint32_t hi, uint32_t lo, uint32_t s) {
   return (uint32_t)((((uint64_t)hi << 32) | lo) >> (8 * (s & 3)));
 }
+// byte k of the result: selector 0..3 of lo, 4..7 of hi, 12 zero
+inline uint32_t __builtin_amdgcn_perm(uint32_t hi, uint32_t lo, uint32_t sel) {
+  uint32_t r = 0;
+  for (int k = 0; k < 4; k++) {
+    const uint32_t q = (sel >> (8 * k)) & 0xFFu;
+    r |= (q < 4 ? (lo >> (8 * q)) & 0xFFu : (q < 8 ? (hi >> (8 * (q - 4))) & 0xFFu : 0u)) << (8 * k);
+  }
+  return r;
+}
 inline void __builtin_amdgcn_s_sleep(int) { }
 typedef int16_t emu_s16x2 __attribute__((vector_size(4)));
 inline int __builtin_amdgcn_sdot2(emu_s16x2 a, emu_s16x2 b, int c, bool) { return c + a[0] * b[0] + a[1] * b[1]; }
