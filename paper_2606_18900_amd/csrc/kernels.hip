@@ -1797,9 +1797,9 @@ int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, 
 // instruction a byte (two a pair, two half segments in one packed 16-bit
 // register) replace the rest of the chain, and one more gives the d, summed up
 // with their weights by dot products.
-// 128 MiB in 8192 blocks, blocks and hash over the hashes together: 80 us (58 and 25);
-// with the chain in one thread per block (292 us) and one thread for the hash
-// over the hashes (1353 us) it was 1716 us.  Bound by the passes'
+// 128 MiB in 8192 blocks, blocks and hash over the hashes together: 71 us (57
+// and 16); with the chain in one thread per block (292 us) and one thread for
+// the hash over the hashes (1353 us) it was 1716 us.  Bound by the passes'
 // instructions, not by memory (27 us at a copy's rate).
 namespace {
 
@@ -1869,15 +1869,15 @@ __device__ __forceinline__ void fnv_bit(uint32_t k, uint32_t xa, uint32_t xb, ui
   c = (c ^ all) & 1u;
 }
 
-// The sum that this lane's segment contributes at its end: the 64 bytes at p
-// or, with PART, only the last m of them (0: p is not read).  low: the low byte
-// of the hash before the round, then after it.
-template <uint32_t NW, bool PART>
-__device__ __forceinline__ uint64_t fnv_segment(const uint8_t* p, uint32_t m, uint32_t& low, uint32_t wv,
+// The sum that this lane's segment contributes at its end, the 64 bytes at p
+// (have: it has one; p is not read else).  low: the low byte of the hash before
+// the round, then after it.
+template <uint32_t NW>
+__device__ __forceinline__ uint64_t fnv_segment(const uint8_t* p, bool have, uint32_t& low, uint32_t wv,
                                                 uint32_t (*bits)[8]) {
   constexpr FnvWeights kW = fnv_weights();
   uint32_t w[kSeg / 4] = {};
-  if (!PART || m) {
+  if (have) {
 #pragma unroll
     for (uint32_t q = 0; q < kSeg / 16; q++) {
       const u32x4 v = ld128(p + 16 * q);
@@ -1886,33 +1886,28 @@ __device__ __forceinline__ uint64_t fnv_segment(const uint8_t* p, uint32_t m, ui
     }
   }
   // byte i of the first half segment with byte i of the second
-  u16x2 pr[kSeg / 2], on[kSeg / 2];
+  u16x2 pr[kSeg / 2];
 #pragma unroll
-  for (uint32_t i = 0; i < kSeg / 2; i++) {
+  for (uint32_t i = 0; i < kSeg / 2; i++)
     pr[i] = (u16x2)__builtin_amdgcn_perm(w[kSeg / 8 + i / 4], w[i / 4], 0x0C040C00u + 0x00010001u * (i % 4));
-    on[i] = (u16x2){(uint16_t)(i + m >= kSeg ? 0xFFFFu : 0u), (uint16_t)(i + m >= kSeg / 2 ? 0xFFFFu : 0u)};
-  }
-  uint32_t sa = 0, sb = 0, next = 0;
-  if (!PART) {                                   // bit 0: the parity of the bytes' bits 0
-    uint32_t xa = 0, xb = 0;
+  // bit 0: the parity of the bytes' bits 0
+  uint32_t xa = 0, xb = 0, sa = 0, sb = 0, next = low & 1u;
 #pragma unroll
-    for (uint32_t q = 0; q < kSeg / 8; q++) {
-      xa ^= w[q];
-      xb ^= w[kSeg / 8 + q];
-    }
-    next = low & 1u;
-    fnv_bit<NW>(0, __builtin_popcount(xa & 0x01010101u) & 1u, __builtin_popcount(xb & 0x01010101u) & 1u, next, sa, sb, wv, bits);
+  for (uint32_t q = 0; q < kSeg / 8; q++) {
+    xa ^= w[q];
+    xb ^= w[kSeg / 8 + q];
   }
+  xa = __builtin_popcount(xa & 0x01010101u) & 1u;
+  xb = __builtin_popcount(xb & 0x01010101u) & 1u;
+  fnv_bit<NW>(0, xa, xb, next, sa, sb, wv, bits);
+  const uint32_t mine = have ? 1u : 0u;
 #pragma unroll 1
-  for (uint32_t k = PART ? 0 : 1; k < 8; k++) {
+  for (uint32_t k = 1; k < 8; k++) {
     u16x2 l = {(uint16_t)sa, (uint16_t)sb};
 #pragma unroll
-    for (uint32_t i = 0; i < kSeg / 2; i++) {
-      const u16x2 x = (l ^ pr[i]) * (uint16_t)0xb3;
-      l = PART ? (x & on[i]) | (l & ~on[i]) : x;
-    }
+    for (uint32_t i = 0; i < kSeg / 2; i++) l = (l ^ pr[i]) * (uint16_t)0xb3;
     uint32_t c = (low >> k) & 1u;
-    fnv_bit<NW>(k, ((uint32_t)l[0] >> k) & 1u, ((uint32_t)l[1] >> k) & 1u, c, sa, sb, wv, bits);
+    fnv_bit<NW>(k, ((uint32_t)l[0] >> k) & mine, ((uint32_t)l[1] >> k) & mine, c, sa, sb, wv, bits);
     next |= c << k;
   }
   low = next;
@@ -1921,40 +1916,33 @@ __device__ __forceinline__ uint64_t fnv_segment(const uint8_t* p, uint32_t m, ui
   int32_t acc[4] = {0, 0, 0, 0};
 #pragma unroll
   for (uint32_t i = 0; i < kSeg / 2; i++) {
-    const u16x2 x = l ^ pr[i];
-    u16x2 d = x - l;
-    const u16x2 y = x * (uint16_t)0xb3;
-    if (PART) d = d & on[i];
-    l = PART ? (y & on[i]) | (l & ~on[i]) : y;
+    const u16x2 x = l ^ pr[i], d = x - l;
+    l = x * (uint16_t)0xb3;
 #pragma unroll
     for (uint32_t k = 0; k < 4; k++) {
       const s16x2 c = {(int16_t)(kW.w[k][i] & 0xFFFFu), (int16_t)(kW.w[k][i] >> 16)};
       acc[k] = __builtin_amdgcn_sdot2((s16x2)d, c, acc[k], false);
     }
   }
-  return (uint64_t)(int64_t)acc[0] + ((uint64_t)(int64_t)acc[1] << 16) + ((uint64_t)(int64_t)acc[2] << 32) +
-         ((uint64_t)(int64_t)acc[3] << 48);
+  const uint64_t sum = (uint64_t)(int64_t)acc[0] + ((uint64_t)(int64_t)acc[1] << 16) +
+                       ((uint64_t)(int64_t)acc[2] << 32) + ((uint64_t)(int64_t)acc[3] << 48);
+  return have ? sum : 0;
 }
 
 // A workgroup of NW waves extends the hash h by the n bytes at p, kChunk * NW
 // bytes a round (NW = 1: each wave on its own bytes, no barrier).  Every lane
 // returns the hash.  Whole rounds only carry the low byte from one to the
 // next: each lane's sums are weighted and added up over the rounds, and the
-// lanes put together once at the end.  The last, shorter round takes whole
-// segments and one segment whose last m bytes are the data's (its window
-// begins in the segment before).
+// lanes put together once at the end.  Then a round of the whole segments that
+// are left, and the last bytes (less than a segment) one by one.
 template <uint32_t NW>
 __device__ uint64_t fnv_extend(uint64_t h, const uint8_t* p, uint64_t n, uint64_t (*part)[2], uint32_t (*bits)[8]) {
-  if (n < kSeg) {
-    for (uint64_t i = 0; i < n; i++) h = (h ^ p[i]) * kFnvPrime;
-    return h;
-  }
   const uint32_t lane = lane_id(), wv = NW > 1 ? uni(threadIdx.x >> 6) : 0u;
   const uint32_t o = wv * kChunk + lane * kSeg;                   // this lane's segment
   uint64_t at = 0, T = 0;
   uint32_t low = (uint32_t)h & 0xFFu;
   for (; at + kChunk * NW <= n; at += kChunk * NW) {
-    T = T * fnv_pow(kChunk * NW) + fnv_segment<NW, false>(p + at + o, kSeg, low, wv, bits);
+    T = T * fnv_pow(kChunk * NW) + fnv_segment<NW>(p + at + o, true, low, wv, bits);
     h *= fnv_pow(kChunk * NW);
   }
   if (at) {
@@ -1975,12 +1963,12 @@ __device__ uint64_t fnv_extend(uint64_t h, const uint8_t* p, uint64_t n, uint64_
       __syncthreads();
     }
   }
-  if (at < n) {                                                   // the rest, less than a round
-    const uint32_t todo = (uint32_t)(n - at);
-    const uint32_t m = o < todo ? min(kSeg, todo - o) : 0u;
+  const uint32_t todo = (uint32_t)(n - at) & ~(kSeg - 1);         // whole segments, less than a round
+  if (todo) {
     const uint32_t end = min(todo, (wv + 1) * kChunk);            // of the wave's bytes
-    uint64_t R = fnv_segment<NW, true>(p + at + o + m - kSeg, m, low, wv, bits);
-    R *= fnv_pow_at(o + m < end ? end - o - m : 0u);
+    const bool have = o < todo;
+    uint64_t R = fnv_segment<NW>(p + at + o, have, low, wv, bits);
+    R *= fnv_pow_at(have ? end - o - kSeg : 0u);
     for (uint32_t s = 32; s; s >>= 1) R += __shfl(R, (int)(lane + s) & 63);
     const uint32_t len = wv * kChunk < todo ? end - wv * kChunk : 0u;
     if (NW == 1) {
@@ -1995,7 +1983,12 @@ __device__ uint64_t fnv_extend(uint64_t h, const uint8_t* p, uint64_t n, uint64_
       for (uint32_t q = 0; q < NW; q++) h = h * part[q][1] + part[q][0];
       __syncthreads();
     }
+    at += todo;
   }
+  const uint32_t left = (uint32_t)(n - at);                       // less than a segment
+  const uint32_t v = lane < left ? p[at + lane] : 0u;
+#pragma unroll 1
+  for (uint32_t i = 0; i < left; i++) h = (h ^ __builtin_amdgcn_readlane(v, i)) * kFnvPrime;
   return h;
 }
 
