@@ -2799,8 +2799,10 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   // Batches on an archive of less than 256 blocks stay with one workgroup: a
   // program that serves such an archive (tests/test_gpu_serve.py) counts on a
   // batch of 3 MiB being on the device for the millisecond in which the next
-  // ones arrive (3 ms so, 0.14 ms with the grid below).
-  if (R.mode == 2 && v.n_blocks < 256)
+  // ones arrive (3 ms so, 0.14 ms with the grid below).  The streams of a split
+  // container are not served so: 266 reads of a 1.3 MB one 1640 us with one
+  // workgroup a stream, 195 us with the grid.
+  if (R.mode == 2 && v.n_blocks < 256 && !h->of_split)
     hipLaunchKernelGGL(k_req_gather_one, dim3(1), dim3(256), 0, s, R);
   else
     hipLaunchKernelGGL(k_req_gather, dim3((uint32_t)std::min<uint64_t>(g_gather, 16ull * h->n_cu)), dim3(256), 0, s, R, parts);

@@ -91,4 +91,5 @@ struct lz_handle {
   uint32_t level_count[kMaxLevels];   // host copy of the whole-file level histogram
   uint64_t literal_bytes;             // sum of n_lit over blocks
   uint64_t payload_bytes;             // end of the last block payload
+  bool of_split = false;              // a stream of a split container
 };

@@ -407,6 +407,7 @@ extern "C" int lz_split_open(const uint8_t* d_container, uint64_t len, void* d_w
     sp->nblocks[k] = sub[k].n_blocks;
     sp->block_log2[k] = sub[k].block_log2;
     rc = lz_open(d_container + h.sub_off[k], h.sub_len[k], w + L.ws[k], std::max<uint64_t>(wsb[k], 256), s, &sp->sub[k]);
+    if (!rc) sp->sub[k]->of_split = true;
   }
   if (rc) { lz_split_close(sp); return rc; }
   sp->d_hs = reinterpret_cast<const uint64_t*>(d_container + h.off_h);
