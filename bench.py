@@ -30,8 +30,8 @@ HBM_PEAK_GBPS = 8000.0      # MI355X HBM3E
 # WRITE_SIZE, of the k_decode dispatch), each scaled by what the same counter reads for a 1 GiB device copy
 # (`bench.py --legs copy`: FETCH_SIZE x 1.99995, WRITE_SIZE x 1.0).  Reported
 # only while the decoder source is the one the counters were taken on.
-PMC_TRAFFIC = {"kernels_sha256_16": "b63b03877cdd266a", "bytes": 1 << 30,
-               "fetch": 618814353, "write": 1345668448}
+PMC_TRAFFIC = {"kernels_sha256_16": "c847d39ce9a6b1e0", "bytes": 1 << 30,
+               "fetch": 618878906, "write": 1345668448}
 
 
 def log(msg: str) -> None:
