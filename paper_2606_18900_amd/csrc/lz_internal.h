@@ -76,6 +76,7 @@ enum : uint32_t {
   kCtlLeft = 9,       // decode: workgroups of the running launch that have finished
   kCtlTotal = 10,     // u64: total output bytes of the batch
   kCtlPairs = 12,     // u64: (request, covering block) pairs of the batch
+  kCtlUnlisted = 14,  // lz_open: a block copies from one that its dependency list lacks
   kCtlLevelCnt = 16,  // 64 level counters of the closure queue
   kCtlDiag = 80,      // first watchdog: site, block, dependency, seen, expected
   kCtlClock = 96,     // u64[16]: stage clocks of an instrumented build (LZ_STAGE_CLOCKS)
@@ -91,5 +92,6 @@ struct lz_handle {
   uint32_t level_count[kMaxLevels];   // host copy of the whole-file level histogram
   uint64_t literal_bytes;             // sum of n_lit over blocks
   uint64_t payload_bytes;             // end of the last block payload
+  bool deps_listed = true;            // every block's list names all blocks that it copies from
   bool of_split = false;              // a stream of a split container
 };

@@ -27,6 +27,8 @@ extern "C" const char* lz_last_error(void) { return g_err; }
 // launchers (kernels.hip)
 size_t lz_decode_smem_bytes();
 int lz_launch_setup(lz_handle* h, hipStream_t s);
+int lz_launch_check_deps(lz_handle* h, hipStream_t s);
+int lz_launch_clear_ctl(lz_handle* h, hipStream_t s);
 int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s);
 int lz_launch_verify(lz_handle* h, const uint8_t* d_out, uint64_t b0, uint64_t nb, uint64_t* d_tree,
                      void* scratch, hipStream_t s);
@@ -293,7 +295,14 @@ extern "C" int lz_open(const uint8_t* d_archive, uint64_t len, void* d_ws, uint6
   for (const uint32_t d : deps) flags[d] = 0;
   if (!rc) rc = hip_check(hipMemcpyAsync(h->ws.flags, flags.data(), 4 * flags.size(), hipMemcpyHostToDevice, s), "lz_open: flags upload");
   if (!rc) rc = lz_launch_setup(h, s);
+  uint32_t unlisted = 0;
+  if (!rc && n_levels > 1) {
+    rc = lz_launch_check_deps(h, s);
+    if (!rc) rc = hip_check(hipMemcpyAsync(&unlisted, h->ws.ctl + kCtlUnlisted, 4, hipMemcpyDeviceToHost, s), "lz_open: dependency check copy");
+    if (!rc) rc = lz_launch_clear_ctl(h, s);
+  }
   if (!rc) rc = hip_check(hipStreamSynchronize(s), "lz_open: sync");
+  h->deps_listed = !unlisted;
   if (rc) { delete h; return rc; }
   *out = h;
   return LZ_OK;
