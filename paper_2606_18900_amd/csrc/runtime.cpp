@@ -292,7 +292,7 @@ extern "C" int lz_open(const uint8_t* d_archive, uint64_t len, void* d_ws, uint6
   rc = hip_check(hipMemcpyAsync(h->ws.queue, queue.data(), 4 * queue.size(), hipMemcpyHostToDevice, s), "lz_open: queue upload");
   if (!rc) rc = hip_check(hipMemcpyAsync(h->ws.level_ptr, lptr.data(), 4 * 65, hipMemcpyHostToDevice, s), "lz_open: level upload");
   std::vector<uint32_t> flags(std::max<uint64_t>(nb, 1), kFlagLeaf);
-  for (const uint32_t d : deps) flags[d] = 0;
+  for (uint64_t k = 0; nb && k < ndeps; k++) flags[deps[k]] = 0;   // no blocks: no list was checked
   if (!rc) rc = hip_check(hipMemcpyAsync(h->ws.flags, flags.data(), 4 * flags.size(), hipMemcpyHostToDevice, s), "lz_open: flags upload");
   if (!rc) rc = lz_launch_setup(h, s);
   uint32_t unlisted = 0;

@@ -26,6 +26,8 @@ static uint8_t* aligned(size_t n) {
   return (uint8_t*)p;
 }
 
+static bool differs(const void* a, const void* b, size_t n) { return n && std::memcmp(a, b, n); }
+
 #define CHECK(x) do { int rc_ = (x); if (rc_) { std::fprintf(stderr, "%s -> %d: %s\n", #x, rc_, lz_last_error()); return 1; } } while (0)
 
 int main(int argc, char** argv) {
@@ -43,7 +45,7 @@ int main(int argc, char** argv) {
   uint8_t* out = aligned(N + 256);
   CHECK(lz_decode_all(h, out, N + 256, nullptr));
   CHECK(lz_sync_status(h, nullptr));
-  if (std::memcmp(out, src.data(), N)) { std::fprintf(stderr, "whole-file decode differs\n"); return 1; }
+  if (differs(out, src.data(), N)) { std::fprintf(stderr, "whole-file decode differs\n"); return 1; }
   // ranges
   const uint64_t scr_len = 256 + 64 * 1024 + info.n_blocks * B;
   uint8_t* scr = aligned(scr_len);
@@ -54,7 +56,7 @@ int main(int argc, char** argv) {
     std::memset(scr, 0xAA, scr_len);
     CHECK(lz_decode_range(h, offs[k], lens[k], r, scr, scr_len, nullptr));
     CHECK(lz_sync_status(h, nullptr));
-    if (std::memcmp(r, src.data() + offs[k], lens[k])) { std::fprintf(stderr, "range %d differs\n", k); return 1; }
+    if (differs(r, src.data() + offs[k], lens[k])) { std::fprintf(stderr, "range %d differs\n", k); return 1; }
     std::free(r);
   }
   // reads (records of four lines)
@@ -74,7 +76,7 @@ int main(int argc, char** argv) {
     CHECK(lz_sync_status(h, nullptr));
     for (int k = 0; k < 4; k++) {
       const uint64_t a = rs[ids_h[k]], b = rs[ids_h[k] + 1];
-      if (offsets[k + 1] - offsets[k] != b - a || std::memcmp(r + offsets[k], src.data() + a, b - a)) {
+      if (offsets[k + 1] - offsets[k] != b - a || differs(r + offsets[k], src.data() + a, b - a)) {
         std::fprintf(stderr, "read %d differs\n", k);
         return 1;
       }
@@ -93,7 +95,7 @@ int main(int argc, char** argv) {
     std::memset(scr, 0xAA, scr_len);
     CHECK(lz_decode_range(h, offs[k], lens[k], r, scr, scr_len, nullptr));
     CHECK(lz_sync_status(h, nullptr));
-    if (std::memcmp(r, src.data() + offs[k], lens[k])) { std::fprintf(stderr, "range %d differs (8 kernels)\n", k); return 1; }
+    if (differs(r, src.data() + offs[k], lens[k])) { std::fprintf(stderr, "range %d differs (8 kernels)\n", k); return 1; }
     std::free(r);
   }
   // a batch of two ranges (and two reads when there is a read index)
@@ -130,7 +132,7 @@ int main(int argc, char** argv) {
         }
         want.insert(want.end(), src.begin() + a0, src.begin() + b0);
       }
-      if (offsets[nreq] != want.size() || std::memcmp(r, want.data(), want.size())) {
+      if (offsets[nreq] != want.size() || differs(r, want.data(), want.size())) {
         std::fprintf(stderr, "batch differs (plan_blocks %u)\n", pb);
         return 1;
       }

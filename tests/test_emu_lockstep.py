@@ -10,6 +10,7 @@ the branch, or hang.  (Found this way and fixed: the one-workgroup request
 planner let waves read the closure list's length at different times within a
 round, so they could leave its loop in different rounds.)"""
 import os
+import struct
 import subprocess
 import sys
 
@@ -80,3 +81,35 @@ def test_kernels_under_lockstep_emulation(emu, orc, tmp_path):
             fails.append("%s: rc %d\n%s\n%s" % (name, p.returncode, out.decode(errors="replace")[-500:],
                                               err.decode(errors="replace")[-3000:]))
     assert not fails, "\n".join(fails)
+
+
+def _run(emu, tmp_path, archive, source, *more):
+    (tmp_path / "t.lz").write_bytes(archive)
+    (tmp_path / "t.src").write_bytes(source)
+    env = dict(os.environ, LZ_EMU_LIMIT_S="60", ASAN_OPTIONS="detect_leaks=1")
+    return subprocess.run([emu, str(tmp_path / "t.lz"), str(tmp_path / "t.src"), *more], env=env, timeout=600,
+                          stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+
+
+def test_dependencies_of_an_empty_archive_are_not_followed(emu, orc, tmp_path):
+    """An archive of no blocks whose dependency list is not empty: no block's
+    list holds the entries, so nothing has checked that they name blocks."""
+    a = bytearray(orc.encode(b""))
+    idx, pay = struct.unpack_from("<QQ", a, 80)
+    ptr = struct.unpack_from("<Q", a, 72)[0]
+    ids = struct.pack("<64I", *([1 << 20] * 64))
+    struct.pack_into("<Q", a, ptr, 64)
+    a[idx:idx] = ids
+    struct.pack_into("<Q", a, 88, pay + len(ids))
+    _seal(a)
+    r = _run(emu, tmp_path, bytes(a), b"")
+    assert r.returncode == 0 and "emu ok" in r.stdout, r.stderr[-3000:]
+
+
+def _seal(a):
+    """Total length and header hash of an archive that was changed."""
+    struct.pack_into("<Q", a, 104, len(a))
+    h = 0xcbf29ce484222325
+    for c in a[:120]:
+        h = (h ^ c) * 0x100000001b3 % 2 ** 64
+    struct.pack_into("<Q", a, 120, h)
