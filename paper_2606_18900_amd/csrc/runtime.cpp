@@ -176,7 +176,7 @@ extern "C" int lz_open(const uint8_t* d_archive, uint64_t len, void* d_ws, uint6
   if (!rc) rc = hip_check(hipStreamSynchronize(s), "lz_open: sync");
   if (rc) return rc;
   const uint64_t ndeps = rd64(meta.data() + v.off_dep_ptr + 8 * nb);
-  if (v.off_dep_idx < v.off_dep_ptr + 8 * (nb + 1) || !fits(v.off_dep_idx, 4 * ndeps, len)) return lz_fail(LZ_EFORMAT, "dependency list out of bounds");
+  if (ndeps > len / 4 || v.off_dep_idx < v.off_dep_ptr + 8 * (nb + 1) || !fits(v.off_dep_idx, 4 * ndeps, len)) return lz_fail(LZ_EFORMAT, "dependency list out of bounds");
   if (v.off_payload < v.off_dep_idx + 4 * ndeps || v.off_payload > len || (v.off_payload & 15))
     return lz_fail(LZ_EFORMAT, "payload out of bounds or misaligned");
   std::vector<uint32_t> deps(ndeps);
@@ -187,7 +187,7 @@ extern "C" int lz_open(const uint8_t* d_archive, uint64_t len, void* d_ws, uint6
   }
   const uint64_t pay_end = v.kind == 1 ? v.off_ridx : len;
   if (v.kind == 1) {
-    if (v.off_ridx < v.off_payload || !fits(v.off_ridx, 8 * (v.n_reads + 1), len)) return lz_fail(LZ_EFORMAT, "read index out of bounds");
+    if (v.n_reads >= len / 8 || v.off_ridx < v.off_payload || !fits(v.off_ridx, 8 * (v.n_reads + 1), len)) return lz_fail(LZ_EFORMAT, "read index out of bounds");
   } else if (v.off_ridx || v.n_reads) {
     return lz_fail(LZ_EFORMAT, "read index present without FASTQ kind");
   }

@@ -113,3 +113,20 @@ def _seal(a):
     for c in a[:120]:
         h = (h ^ c) * 0x100000001b3 % 2 ** 64
     struct.pack_into("<Q", a, 120, h)
+
+
+@pytest.mark.parametrize("what", ["dependencies", "reads"])
+def test_counts_whose_size_wraps_are_refused(emu, orc, tmp_path, what):
+    """Counts so large that their tables' sizes in bytes are 0 mod 2^64 lie
+    outside the archive: LZ_EFORMAT, not an allocation that throws."""
+    from gen.fastq import fastq
+    x, _ = fastq(n_records=5, seed=1)
+    a = bytearray(orc.encode(x, kind=1))
+    if what == "dependencies":
+        nb, ptr = struct.unpack_from("<Q", a, 32)[0], struct.unpack_from("<Q", a, 72)[0]
+        struct.pack_into("<Q", a, ptr + 8 * nb, 2 ** 62)
+    else:
+        struct.pack_into("<Q", a, 40, 2 ** 61 - 1)
+    _seal(a)
+    r = _run(emu, tmp_path, bytes(a), x)
+    assert r.returncode == 1 and "-> -2:" in r.stderr and "out of bounds" in r.stderr, r.stderr[-3000:]
