@@ -919,8 +919,9 @@ __device__ __forceinline__ void copy_long(Smem& S, const DevArgs& A, uint64_t sb
 // a finished block's flag.  The next place and block go to S.nit and S.nb
 // (kNext of the result; unset after corrupt data); kPrepared: that block has
 // been prepared meanwhile, by waves 1..3 while wave 0 resolved b's in-block
-// matches; kUsed: this block is still to be published.  Every loop below is bounded by values read from global memory
-// (directory, stream headers) or by the spin limit.
+// matches; kUsed: this block is still to be published, if others copy from it,
+// corrupt or not.  Every loop below is bounded by values read from global
+// memory (directory, stream headers) or by the spin limit.
 constexpr uint32_t kPrepared = 1, kNext = 2, kUsed = 4;
 __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint32_t b, uint32_t qb,
                                                  uint32_t total, uint32_t it, uint32_t epoch) {
@@ -1475,7 +1476,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
   CLK_MARK(S, 7);
   if (S.err) {
     if (t == 0) latch(A.ctl, kStCorrupt);
-    return kNext | kUsed | (prepared ? kPrepared : 0u);
+    return kNext | (ov ? 0u : kUsed) | (prepared ? kPrepared : 0u);   // ov: published, if at all
   }
 
   // ---- stage 5, unless wave 0 has done it
@@ -1587,7 +1588,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(Jobs<N> J) {   // 3 waves per
   while (it < total) {
     if (!prepared) prep_tile(S, A, b);
     const uint32_t r = decode_block(S, A, b, qb, total, it, epoch);
-    const bool publish = A.flow && (r & kUsed);
+    const bool publish = A.flow && (r & kUsed) && uni(S.used);   // S.used is still this block's
     if (publish) vm_wait();                // this wave's stores have completed
     __syncthreads();
     if (publish && t == 0) {
@@ -1610,7 +1611,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(Jobs<N> J) {   // 3 waves per
     if (left + 1 == min(A.nwg, total)) {
       A.ctl[kCtlTicket] = 0;
       A.ctl[kCtlLeft] = 0;
-      A.ctl[kCtlEpoch] = epoch;
+      A.ctl[kCtlEpoch] = epoch < kMaxEpoch ? epoch : 0u;
     }
   }
 #ifdef LZ_STAGE_CLOCKS
@@ -2175,6 +2176,7 @@ struct ReqArgs {
   uint8_t* slots;
   uint64_t max_slots;
   uint32_t* mark;
+  uint32_t* flags;
   uint64_t* addr;
   uint32_t* rqueue;
   uint32_t* rlevel_ptr;
@@ -2207,6 +2209,17 @@ __device__ __forceinline__ void mark_push(const ReqArgs& R, uint32_t b, uint32_t
   __hip_atomic_store(R.list + i, ((uint64_t)epoch << 32) | b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The decode epochs near their end (one workgroup): flags of any earlier epoch
+// are cleared, so that none is met again after the epochs have started over;
+// true if so, and the caller resets the epoch after a barrier.  Whole-file
+// decodes need no such care: each sets every flag that is ever set.
+__device__ __forceinline__ bool renew_flags(const ReqArgs& R) {
+  if (R.ctl[kCtlEpoch] < kRenewEpoch) return false;
+  for (uint64_t i = threadIdx.x; i < R.n_blocks; i += blockDim.x)
+    if (R.flags[i] != kFlagLeaf) R.flags[i] = 0;
+  return true;
+}
+
 // One workgroup.  First the address-table entries of the previous call's
 // closure (still in the work list) are cleared, so that afterwards exactly the
 // blocks of this call's closure have an address: a match whose source lies in
@@ -2219,9 +2232,11 @@ __global__ void __launch_bounds__(256) k_req_begin(ReqArgs R) {
     const uint32_t b = (uint32_t)R.list[i];
     if (b < R.n_blocks) R.addr[b] = 0;
   }
+  const bool renew = renew_flags(R);
   __syncthreads();
   if (t < 64) R.ctl[kCtlLevelCnt + t] = 0;
   if (t == 0) {
+    if (renew) R.ctl[kCtlEpoch] = 0;
     R.ctl[kCtlREpoch] += 1;
     R.ctl[kCtlListTail] = 0;
     R.ctl[kCtlListHead] = 0;
@@ -2475,6 +2490,7 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
       if (b < R.n_blocks) R.addr[b] = 0;
     }
   }
+  const bool renew = renew_flags(R);
   if (R.lmark)
     for (uint32_t i = t; i < ((uint32_t)R.n_blocks + 31) / 32; i += kPlanWG) s_bits[i] = 0;
   if (t < 64) lvl_cnt[t] = 0;
@@ -2493,6 +2509,7 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
   __syncthreads();
   const uint32_t epoch = s_epoch;
   const uint32_t nreq = s_nreq;
+  if (renew && t == 0) R.ctl[kCtlEpoch] = 0;
   // spans, output offsets and covering-block counts, 1024 requests a round
   uint64_t carry_len = 0, carry_cnt = 0;
   for (uint32_t c0 = 0; c0 < nreq; c0 += kPlanWG) {
@@ -2794,6 +2811,7 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   R.max_slots = (scratch_len - slots_off) / B;
   R.direct = (R.mode == 0 && ((uintptr_t)d_out & 15) == 0) ? 1u : 0u;
   R.mark = h->ws.mark;
+  R.flags = h->ws.flags;
   R.addr = h->ws.addr;
   R.rqueue = h->ws.rqueue;
   R.rlevel_ptr = h->ws.rlevel_ptr;

@@ -24,8 +24,10 @@ constexpr uint32_t kMaxOffsetWidth = 5;   // absolute offsets below 2^40
 constexpr uint32_t kMaxLevels = 64;
 
 // Workspace::flags of a block that no block copies from: nothing waits for it,
-// so its flag is never set
-constexpr uint32_t kFlagLeaf = 0xFFFFFFFFu;
+// so its flag is never set.  Epochs run from 1 to kMaxEpoch and start again;
+// request calls, which set the flags of some blocks only, start them again from
+// kRenewEpoch on, with the flags cleared.
+constexpr uint32_t kFlagLeaf = 0xFFFFFFFFu, kMaxEpoch = kFlagLeaf - 1, kRenewEpoch = 0xF0000000u;
 
 // status bits latched by kernels in the workspace status word
 enum : uint32_t {

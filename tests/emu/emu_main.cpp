@@ -1,12 +1,15 @@
 // Test driver of the CPU emulation: decode an archive through the C ABI
 // (whole file, three ranges, and four reads when it has a read index) and
-// compare every byte with the source.  Prints "emu ok" and exits 0 on success.
+// compare every byte with the source.  With a third argument, the epoch of the
+// handle's last decode is set to that first, and five decodes follow.  Prints
+// "emu ok" and exits 0 on success.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <vector>
 
 #include "lz.h"
+#include "lz_internal.h"
 
 static std::vector<uint8_t> slurp(const char* p) {
   std::vector<uint8_t> v;
@@ -43,6 +46,15 @@ int main(int argc, char** argv) {
   CHECK(lz_open(arc, av.size(), ws, info.workspace_bytes, nullptr, &h));
   const uint64_t N = info.n, B = 1ull << info.block_log2;
   uint8_t* out = aligned(N + 256);
+  if (argc > 3) {
+    h->ws.ctl[kCtlEpoch] = (uint32_t)std::strtoul(argv[3], nullptr, 0);
+    for (int k = 0; k < 5; k++) {
+      std::memset(out, 0xAA, N);
+      CHECK(lz_decode_all(h, out, N + 256, nullptr));
+      CHECK(lz_sync_status(h, nullptr));
+      if (differs(out, src.data(), N)) { std::fprintf(stderr, "decode %d differs\n", k); return 1; }
+    }
+  }
   CHECK(lz_decode_all(h, out, N + 256, nullptr));
   CHECK(lz_sync_status(h, nullptr));
   if (differs(out, src.data(), N)) { std::fprintf(stderr, "whole-file decode differs\n"); return 1; }

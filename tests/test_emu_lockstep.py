@@ -130,3 +130,13 @@ def test_counts_whose_size_wraps_are_refused(emu, orc, tmp_path, what):
     _seal(a)
     r = _run(emu, tmp_path, bytes(a), x)
     assert r.returncode == 1 and "-> -2:" in r.stderr and "out of bounds" in r.stderr, r.stderr[-3000:]
+
+
+def test_completion_epochs_start_again(emu, orc, tmp_path):
+    """A handle's 2^32nd decode: the launch after the last epoch begins with
+    flags that no earlier launch has left, and the marks of blocks that nothing
+    copies from are never an epoch."""
+    x = _data("motifs")[:1500]
+    a = orc.encode(x, **CASES["deep_64"][1])
+    r = _run(emu, tmp_path, a, x, "0xFFFFFFFC")
+    assert r.returncode == 0 and "emu ok" in r.stdout, r.stderr[-3000:]
