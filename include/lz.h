@@ -100,8 +100,10 @@ typedef struct lz_tuning {
                            dependency level                               */
   uint32_t wg_per_cu;   /* grid = wg_per_cu * CUs workgroups (a launch takes at
                            most its block count); 1..4, default 3            */
-  uint32_t spin_limit;  /* watchdog: max polls of a dependency flag before the
-                           kernel gives up with LZ_ECORRUPT (0 = default)     */
+  uint32_t spin_limit;  /* watchdog: max polls in one wait before the kernel
+                           gives up with LZ_ECORRUPT (0 = default, 2^20).  A
+                           smaller limit holds for the planner of large request
+                           calls only: a decode waits for 2^20 polls at least */
   uint32_t req_sync_mode; /* request calls (ranges, reads, batches): the same
                            two modes for the closure decode; default 0     */
   uint32_t plan_blocks; /* request calls expected to cover at most this many

@@ -1714,7 +1714,10 @@ static DevArgs make_args(const lz_handle* h) {
   A.lut = h->ws.lut;
   A.flags = h->ws.flags;
   A.ctl = h->ws.ctl;
-  A.spin_limit = h->tune.spin_limit ? h->tune.spin_limit : (1u << 20);
+  // A wait of the decoder ends by itself unless the archive was changed after
+  // lz_open; 2^20 polls are about a second, so no less than that: a limit that
+  // the caller set for the planner's waits must not fail a valid decode.
+  A.spin_limit = std::max(h->tune.spin_limit, 1u << 20);
   return A;
 }
 
