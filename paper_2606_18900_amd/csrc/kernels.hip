@@ -164,6 +164,14 @@ __device__ __forceinline__ void lds_dma16(const void* src, void* dst) {
 __device__ __forceinline__ void vm_wait() {
   __builtin_amdgcn_s_waitcnt(0xF70);   // vmcnt(0), expcnt and lgkmcnt untouched
 }
+// This wave's stores have completed: what a flag says that is set afterwards.
+// The wait alone is no order to the compiler, which may move relaxed stores
+// across it; the fences are (they cost no instruction here).
+__device__ __forceinline__ void stores_done() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  vm_wait();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+}
 __device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {
@@ -1460,7 +1468,7 @@ __device__ __forceinline__ uint32_t decode_block(Smem& S, const DevArgs& A, uint
     // others may be waiting for this block: stage 5 by wave 0 alone, while the
     // others prepare the next block
     store_tile(lane, 64);
-    vm_wait();
+    stores_done();
     if (lane == 0) __hip_atomic_store(A.flags + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else if (wv != 0 && ov) {
     // the preparation has slack (it ends well before wave 0's passes): it
@@ -1589,7 +1597,7 @@ __global__ void __launch_bounds__(kWG, 3) k_decode(Jobs<N> J) {   // 3 waves per
     if (!prepared) prep_tile(S, A, b);
     const uint32_t r = decode_block(S, A, b, qb, total, it, epoch);
     const bool publish = A.flow && (r & kUsed) && uni(S.used);   // S.used is still this block's
-    if (publish) vm_wait();                // this wave's stores have completed
+    if (publish) stores_done();
     __syncthreads();
     if (publish && t == 0) {
       __hip_atomic_store(A.flags + b, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
