@@ -4,7 +4,7 @@ counts of an encoding.
 Whole-file decode (`tune`): the decode kernel's synchronisation mode (one
 launch whose workgroups wait for the blocks they copy from, or one launch per
 dependency level) and the workgroups per CU of its grid (1..3: the kernel's
-launch bounds and its 52 KB of LDS hold three workgroups per CU, so more only
+launch bounds and its 53.7 KB of LDS hold three workgroups per CU, so more only
 queue).  Every candidate decodes the archive into the same buffer and must
 reproduce the archive's source FNV tree (device hash of the output), so a
 faster but wrong setting can never win.
@@ -20,12 +20,13 @@ fixed when a file is encoded, so they are tuned by re-encoding a sample with
 each candidate, decoding it on the device (verified by the source hash) and
 keeping the fastest decode whose ratio is within `max_ratio_loss` of the
 best.  The LDS tile is not a knob: one 16 KiB block per 256-thread workgroup
-is the shape whose 52 KB of LDS fits three workgroups per CU; a tile of two
+is the shape whose 53.7 KB of LDS fits three workgroups per CU; a tile of two
 blocks needs twice the LDS and halves the resident workgroups.
 
 The median of `reps` timed runs (HIP events on the stream) ranks candidates.
-`tune` and `tune_requests` cache their result in a JSON file keyed by device
-name, archive size, block count, level count and source hash."""
+`tune` and `tune_requests` cache their result in a JSON file keyed by the
+version of the modes, device name, archive size, block count, level count and
+source hash."""
 from __future__ import annotations
 
 import json
@@ -35,6 +36,7 @@ import numpy as np
 import torch
 
 MODES = (0, 1)
+MODES_VERSION = 2                    # raised when a mode comes to mean another launch
 WG_PER_CU = (1, 2, 3)
 REQ_MODES = (0, 1)
 PLAN_BLOCKS = (1, 4096, 65536)       # 1: never one-workgroup planning
@@ -44,8 +46,8 @@ LANES = ((256, 64), (128, 64), (128, 32), (64, 32))
 def _key(arc, what: str = "decode") -> str:
     i = arc.info
     dev = torch.cuda.get_device_name(arc.device)
-    return "%s|%s|n=%d|blocks=%d|levels=%d|fnv=%016x" % (what, dev, i.n, i.n_blocks, i.n_levels,
-                                                         int(i.source_fnv) & (2 ** 64 - 1))
+    return "%s|v%d|%s|n=%d|blocks=%d|levels=%d|fnv=%016x" % (what, MODES_VERSION, dev, i.n, i.n_blocks, i.n_levels,
+                                                             int(i.source_fnv) & (2 ** 64 - 1))
 
 
 def _load(cache_path):
