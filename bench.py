@@ -30,8 +30,18 @@ HBM_PEAK_GBPS = 8000.0      # MI355X HBM3E
 # WRITE_SIZE, of the k_decode dispatch), each scaled by what the same counter reads for a 1 GiB device copy
 # (`bench.py --legs copy`: FETCH_SIZE x 1.99995, WRITE_SIZE x 1.0).  Reported
 # only while the decoder source is the one the counters were taken on.
-PMC_TRAFFIC = {"kernels_sha256_16": "c847d39ce9a6b1e0", "bytes": 1 << 30,
+PMC_TRAFFIC = {"decoder_sha256_16": "c847d39ce9a6b1e0", "bytes": 1 << 30,
                "fetch": 618878906, "write": 1345668448}
+
+
+def decoder_sha(csrc: str) -> str:
+    """Fingerprint of the sources that the decode kernel is compiled from."""
+    import hashlib
+    h = hashlib.sha256()
+    for name in ("kernels.hip", "lz_device.h", "lz_internal.h"):
+        with open(os.path.join(csrc, name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def log(msg: str) -> None:
@@ -836,11 +846,9 @@ def main() -> int:
     match_bytes = N - arc.literal_bytes
     algo = arc.payload_bytes + 32 * nb + dep_bytes + match_bytes + N
     achieved = algo / (kern_ms / 1e3) / 1e9
-    import hashlib
-    with open(os.path.join(ROOT, "paper_2606_18900_amd", "csrc", "kernels.hip"), "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()[:16]
+    sha = decoder_sha(os.path.join(ROOT, "paper_2606_18900_amd", "csrc"))
     traffic = None
-    if (sha == PMC_TRAFFIC["kernels_sha256_16"] and args.bytes == PMC_TRAFFIC["bytes"]
+    if (sha == PMC_TRAFFIC["decoder_sha256_16"] and args.bytes == PMC_TRAFFIC["bytes"]
             and best == 0):
         traffic = PMC_TRAFFIC["fetch"] + PMC_TRAFFIC["write"]
 
