@@ -108,8 +108,8 @@ typedef struct lz_tuning {
                            two modes for the closure decode; default 0     */
   uint32_t plan_blocks; /* request calls expected to cover at most this many
                            blocks are planned by one workgroup in one launch,
-                           larger ones by the eight-kernel path; 1..2^20, 0 =
-                           default 4096                                     */
+                           larger ones by the eight-kernel path; 1 = always by
+                           that; 1..2^20, 0 = default 4096                  */
 } lz_tuning;
 
 typedef struct lz_handle lz_handle;

@@ -2835,9 +2835,10 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   // block or a few more; of a batch 256 blocks a request, but not more than
   // its output holds)
   const uint64_t Bs = 1ull << v.block_log2, pb = h->tune.plan_blocks ? h->tune.plan_blocks : 4096;
-  const bool small = R.mode == 0 ? single_len / Bs + 2 <= pb
-                   : R.mode == 1 ? n_max * (v.max_record_len / Bs + 1) <= pb
-                                 : std::min(n_max * 256, cap / Bs + 2 * n_max) <= pb;
+  const uint64_t covering = R.mode == 0 ? single_len / Bs + 2
+                          : R.mode == 1 ? n_max * (v.max_record_len / Bs + 1)
+                                        : std::min(n_max * 256, cap / Bs + 2 * n_max);
+  const bool small = pb > 1 && covering <= pb;     // 1: never
   R.lmark = v.n_blocks <= kPlanBits ? 1u : 0u;
   const uint32_t g_wide = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(1024, (v.n_blocks + 255) / 256));
   if (small) {

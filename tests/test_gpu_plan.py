@@ -57,3 +57,17 @@ def test_reads_and_batches(arc, n):
         seen.append((st.closure_blocks, st.scratch_slots, st.covering, sb.closure_blocks, sb.scratch_slots, sb.covering))
     assert seen[0] == seen[1] == seen[2]
     A.set_tuning(plan_blocks=4096)
+
+
+def test_one_block_means_never(arc):
+    """plan_blocks 1 takes even a single read to the eight kernels (whose list
+    head, control word 5, moves on; one workgroup leaves it at 0)."""
+    x, starts, A = arc
+    head = A.ws[A.ws.numel() - 512:].view(torch.int32)
+    for plan, wide in ((4096, False), (1, True)):
+        A.set_tuning(plan_blocks=plan)
+        got, offs = A.read_lookup([3])
+        A.sync_status()
+        assert got[:int(offs[-1])].cpu().numpy().tobytes() == x[starts[3]:starts[4]]
+        assert (int(head[5]) > 0) == wide
+    A.set_tuning(plan_blocks=4096)
