@@ -2484,6 +2484,7 @@ __global__ void __launch_bounds__(256) k_req_scatter(ReqArgs R) {
 // for the eight kernels, 55 us here; 256 mixed requests 86 and 19 us.
 constexpr uint32_t kPlanWG = 1024;
 constexpr uint32_t kPlanBits = 1u << 18, kPlanList = 6144;
+constexpr uint32_t kPlanOwn = 8;       // covering blocks that a request's own thread marks
 
 __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
   __shared__ uint32_t s_bits[kPlanBits / 32], s_list[kPlanList];
@@ -2607,7 +2608,9 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
     for (uint64_t g = t; g < pairs; g += kPlanWG) push((uint32_t)((R.a0 >> R.bl) + g));
   } else if (pairs) {
     // a thread per request for its first blocks, then the wave together for
-    // each request that has more
+    // each request that has more, one such request after the other: with its
+    // share at 4, 100 records of six blocks of 64 bytes each took that turn
+    // (18 us of a call of 86; from 16 on a lone thread holds the others up)
     for (uint32_t c0 = 0; c0 < nreq; c0 += kPlanWG) {
       const uint32_t j = c0 + t;
       uint32_t b0 = 0, n = 0;
@@ -2616,11 +2619,11 @@ __global__ void __launch_bounds__(kPlanWG) k_req_plan(ReqArgs R) {
         b0 = (uint32_t)(s0 >> R.bl);
         n = e0 > s0 ? (uint32_t)(((e0 - 1) >> R.bl) - b0 + 1) : 0u;
       }
-      for (uint32_t k = 0; k < min(n, 4u); k++) push(b0 + k);
-      for (uint64_t more = __ballot(n > 4); more; more &= more - 1) {     // wave-uniform
+      for (uint32_t k = 0; k < min(n, kPlanOwn); k++) push(b0 + k);
+      for (uint64_t more = __ballot(n > kPlanOwn); more; more &= more - 1) {     // wave-uniform
         const uint32_t l = (uint32_t)__builtin_ctzll(more);
         const uint32_t nb = __builtin_amdgcn_readlane(n, l), bb = __builtin_amdgcn_readlane(b0, l);
-        for (uint32_t k = 4 + lane; k < nb; k += 64) push(bb + k);
+        for (uint32_t k = kPlanOwn + lane; k < nb; k += 64) push(bb + k);
       }
     }
   }
