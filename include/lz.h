@@ -95,7 +95,10 @@ typedef struct lz_request {
 typedef struct lz_tuning {
   uint32_t sync_mode;   /* whole-file decode: 0 = one launch whose workgroups
                            take the blocks in level order and wait for the
-                           completion flags of the blocks they copy from
+                           completion flags of the blocks they copy from,
+                           except for archives that are known to be faster
+                           or safer a level at a time (few levels of many
+                           blocks below 16 KiB; incomplete dependency lists)
                            (lz_open's default), 1 = one launch per
                            dependency level                               */
   uint32_t wg_per_cu;   /* grid = wg_per_cu * CUs workgroups (a launch takes at

@@ -1795,12 +1795,28 @@ static DevArgs whole_file(const lz_handle* h, uint8_t* out) {
 
 // By ticket only what every block waits for is known to be complete; a level
 // at a time, a source in a lower level is there whether it is listed or not.
-bool lz_one_launch(const lz_handle* h) { return h->tune.sync_mode == 0 && h->deps_listed; }
+static bool one_launch(const lz_handle* h) { return h->tune.sync_mode == 0 && h->deps_listed; }
+
+// Whether that many blocks of the archive are decoded faster a level at a time.
+// By ticket every block costs three updates of counters that all workgroups
+// share (about 85 in a microsecond), and every level but the first one is
+// hidden; a launch per level costs a block's latency each, the less the smaller
+// the blocks.  So few levels of many small blocks are left to launches of their
+// own, those of more blocks than workgroups run at once.  Measured by ticket
+// and per level: 8 MB FASTQ of 1 KiB blocks in 2 levels 159 and 126 us, in 4
+// 163 and 156, in 5 158 and 160; of 2 KiB in 3 108 and 90, in 4 110 and 103
+// (a genome 112 and 142); of 8 KiB in 2 74 and 53, in 3 78 and 72 (a genome
+// 93 and 114); 508 blocks of 16 KiB in 2 51 and 55.
+static bool few_levels(const lz_handle* h) {
+  const uint32_t bl = h->av.block_log2;
+  return h->av.n_levels <= (bl <= 10 ? 4u : bl == 11 ? 3u : bl <= 13 ? 2u : 1u);
+}
+static bool shallow(const lz_handle* h, uint64_t blocks) { return few_levels(h) && blocks > decode_slots(h); }
 
 int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
   DevArgs A = whole_file(h, out);
   const uint32_t slots = decode_slots(h);
-  if (lz_one_launch(h)) {
+  if (one_launch(h) && !shallow(h, h->av.n_blocks)) {
     launch_decode(A, std::min(A.q_end, slots), s);
     return launch_ok("lz_decode_all");
   }
@@ -1816,6 +1832,20 @@ int lz_launch_decode_all(lz_handle* h, uint8_t* out, hipStream_t s) {
     base += c;
   }
   return launch_ok("lz_decode_all");
+}
+
+// Whether n archives are decoded at once (below): all by ticket, and not all of
+// few levels with one that is faster a level at a time: then one after the other
+// (streams of an 8 MB FASTQ in 1 KiB blocks of 2 levels 254 us at once and
+// 208 one by one, of 4 levels 267 and 261; of up to 32 levels 226 and 318).
+bool lz_decode_together(lz_handle* const* h, uint32_t n) {
+  bool all_few = true, any_shallow = false;
+  for (uint32_t k = 0; k < n; k++) {
+    if (!one_launch(h[k])) return false;
+    all_few &= few_levels(h[k]);
+    any_shallow |= h[k]->av.n_levels > 1 && shallow(h[k], h[k]->av.n_blocks);
+  }
+  return !(all_few && any_shallow);
 }
 
 // Whole-file decodes of n <= 4 non-empty archives at once, out[k] the output
@@ -2863,7 +2893,10 @@ int lz_launch_requests(lz_handle* h, const lz_request* d_reqs, const uint32_t* d
   A.addr = h->ws.addr;
   A.out = d_out;
   const uint32_t grid = (uint32_t)std::min<uint64_t>(decode_slots(h), std::max<uint64_t>(1, v.n_blocks));
-  if (h->tune.req_sync_mode == 0 && h->deps_listed && v.n_levels > 1) {
+  // the closure, which is known on the device only, taken as three times the
+  // covering blocks; of a small archive half the blocks at most
+  const bool levels = shallow(h, std::min(3 * std::min(covering, v.n_blocks), v.n_blocks / 2));
+  if (h->tune.req_sync_mode == 0 && h->deps_listed && v.n_levels > 1 && !levels) {
     // scratch slots are whole lines; blocks decoded straight into the output lie
     // at d_out - single_off plus a multiple of the block size
     const uint64_t at = reinterpret_cast<uintptr_t>(d_out) - single_off;

@@ -33,7 +33,7 @@
 #include "lz_device.h"
 #include "lz_internal.h"
 
-bool lz_one_launch(const lz_handle* h);                                                            // kernels.hip
+bool lz_decode_together(lz_handle* const* h, uint32_t n);                                          // kernels.hip
 int lz_launch_decode_many(lz_handle* const* h, uint8_t* const* out, uint32_t n, hipStream_t s);   // kernels.hip
 
 namespace {
@@ -465,13 +465,12 @@ extern "C" int lz_split_decode_all(lz_split* sp, uint8_t* d_out, uint64_t cap, h
   lz_handle* h[4];
   uint8_t* out[4];
   uint32_t n = 0;
-  bool together = true;                     // every stream in one launch
   for (int k = 0; k < 4; k++) {
     if (!sp->slen[k]) continue;
     h[n] = sp->sub[k];
     out[n++] = sp->buf + sp->base[k];
-    together &= lz_one_launch(sp->sub[k]);
   }
+  const bool together = lz_decode_together(h, n);
   int rc = together && n ? lz_launch_decode_many(h, out, n, s) : LZ_OK;
   for (uint32_t k = 0; k < n && !together && !rc; k++) rc = lz_decode_all(h[k], out[k], h[k]->av.n, s);
   if (rc) return rc;
