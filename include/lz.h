@@ -149,7 +149,11 @@ int lz_info_get(const uint8_t* host_archive, uint64_t len, lz_info* out);
  * (EFORMAT), checks device limits (EFORMAT: block_log2 > 14, N >= 2^40, more
  * than 1025 sequences per block possible), then builds the level-ordered block queue and the rANS
  * lookup tables in the workspace (d_ws, ws_len bytes, 256-byte aligned;
- * ECAPACITY if smaller than lz_info.workspace_bytes).  Synchronises s. */
+ * ECAPACITY if smaller than lz_info.workspace_bytes).  The matches are read on
+ * the device: if a dependency list lacks a block that its own block copies
+ * from, every decode of the handle takes a launch per level (a whole-file
+ * decode is then right as long as such a source lies in a lower level; a
+ * request whose closure lacks it is LZ_ECORRUPT).  Synchronises s. */
 int lz_open(const uint8_t* d_archive, uint64_t len, void* d_ws, uint64_t ws_len,
             hipStream_t s, lz_handle** h);
 int lz_close(lz_handle* h);
@@ -229,8 +233,8 @@ int lz_decode_region(lz_handle* h, const lz_fasta_seq* sq, uint64_t start, uint6
  * then a gather into d_out at d_offsets (device, n+1 entries).  d_reqs is a
  * device array of n lz_request.  n_max sizes the device-side request
  * capacity the call was planned for (n <= n_max); the sequence of launches
- * depends only on (handle, n_max), so it can be captured once in a HIP graph
- * and replayed with new request contents.  cap bounds the output; a larger
+ * depends only on the handle, its tuning, n_max and cap, so it can be captured
+ * once in a HIP graph and replayed with new request contents.  cap bounds the output; a larger
  * total is latched as ECAPACITY. */
 int lz_decode_batch(lz_handle* h, const lz_request* d_reqs, const uint32_t* d_n,
                     uint64_t n_max, uint8_t* d_out, uint64_t cap, uint64_t* d_offsets,
@@ -321,8 +325,8 @@ int lz_split_close(lz_split* sp);
 int lz_split_stream(lz_split* sp, uint32_t k, lz_handle** out);
 
 /* d_out[0..N) = the FASTQ file: the four streams are decoded into the
- * workspace (lz_decode_all each), then the records are reassembled in file
- * order on the device. */
+ * workspace (in one launch, or by lz_decode_all one after the other), then the
+ * records are reassembled in file order on the device. */
 int lz_split_decode_all(lz_split* sp, uint8_t* d_out, uint64_t cap, hipStream_t s);
 
 /* Scratch (bytes, 256-byte aligned buffer) of lz_split_decode_range (n = 1)

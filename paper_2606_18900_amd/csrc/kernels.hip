@@ -1554,8 +1554,8 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
 // (Tickets of two or four consecutive blocks, to take fewer, delay the blocks
 // that others wait for: 64 levels 1134 us instead of 600.)
 // A launch per level costs at least a block's latency (28 us) a level:
-// 256 MiB FASTQ (6 levels) 497 us so and 445 us by ticket, 128 MiB genome (7)
-// 468 and 288, 64 MiB FASTQ of 64 levels 1513 and 394.
+// 256 MiB FASTQ (6 levels) 498 us so and 410 us by ticket, 128 MiB genome (7)
+// 405 and 262, 64 MiB FASTQ of 64 levels 1523 and 375.
 // Otherwise a grid-stride slice of the queue's blocks q_begin .. q_end (one
 // level).
 // Jobs: up to four archives in one launch (the streams of a split container).
