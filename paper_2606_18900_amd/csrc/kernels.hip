@@ -1564,14 +1564,13 @@ __device__ __forceinline__ void load_tables(Smem& S, const DevArgs& A) {
 // lays after all other kernels, begins in the code object.  The decoder is 83 KB
 // of code, more than an instruction cache (64 KB for two CUs), and the same
 // instructions wait more or less with their place.  Of all places tried (every
-// 256 bytes of a page, and pages over 160 KB), those 0xe00 bytes into a page
-// from 0x17e00 to 0x1ee00 are the best by far and alike: 256 MiB FASTQ 411 us,
+// 256 bytes of a page of 4 KB, and pages over 160 KB), those 0xe00 bytes into a
+// page from 0x17e00 to 0x1ee00 are the best by far and alike: 256 MiB FASTQ 411 us,
 // 128 MiB genome 259, 4096 reads 181.  0xe00 into other pages it is 433, 273
 // and 208, anywhere else 433, 283 and 208.  The counters show as many
-// instructions and fetches, 15 % fewer instruction cache misses and 10 % fewer
-// cycles of waiting.  A change of size in any kernel of this file moves
-// k_decode<1>: put it back to 0x1ce00 by the size here
-// (tests/test_code_place.py tells where it is).
+// instructions and fetches, and 10 % fewer cycles of waiting.  A change of size
+// in any kernel of this file moves k_decode<1>: put it back to 0x1ce00 by the
+// size here (tests/test_code_place.py tells where it is).
 constexpr uint32_t kPlaceBytes = 0x8000;
 __global__ void __attribute__((used)) k_code_place() {
   asm volatile(".fill %c0, 4, 0xbf800000" ::"i"(kPlaceBytes / 4));   // s_nop
