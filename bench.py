@@ -29,9 +29,9 @@ HBM_PEAK_GBPS = 8000.0      # MI355X HBM3E
 # from two rocprofv3 --pmc runs of `bench.py --legs decode` (FETCH_SIZE, then
 # WRITE_SIZE, of the k_decode dispatch), each scaled by what the same counter reads for a 1 GiB device copy
 # (`bench.py --legs copy`: FETCH_SIZE x 1.99995, WRITE_SIZE x 1.0).  Reported
-# only while the decoder source is the one the counters were taken on.
-PMC_TRAFFIC = {"decoder_sha256_16": "c847d39ce9a6b1e0", "bytes": 1 << 30,
-               "fetch": 618878906, "write": 1345668448}
+# only while the decoder's sources (decoder_sha) are those the counters were taken on.
+PMC_TRAFFIC = {"decoder_sha256_16": "bb3faaf92b6d1a1e", "bytes": 1 << 30,
+               "fetch": 618979213, "write": 1345668448}
 
 
 def decoder_sha(csrc: str) -> str:
