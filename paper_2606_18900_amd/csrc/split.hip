@@ -80,11 +80,12 @@ int parse_head(const uint8_t* a, uint64_t len, Head& h) {
   h.src_fnv = rd64(a + 104);
   h.max_rec = rd32(a + 112);
   const uint64_t tab = 8 * (h.n_reads + 1);
-  if (h.n_reads > (len >> 4) || h.off_h < kSplitHeader || h.off_s < h.off_h + tab || h.off_s + tab > len)
+  if (h.n_reads > (len >> 4) || h.off_s > len || h.off_h > h.off_s || h.off_h < kSplitHeader ||
+      tab > h.off_s - h.off_h || tab > len - h.off_s)
     return lz_fail(LZ_EFORMAT, "split container: record tables out of bounds");
   uint64_t prev = h.off_s + tab;
   for (int k = 0; k < 4; k++) {
-    if ((h.sub_off[k] & 255) || h.sub_off[k] < prev || h.sub_len[k] > len - h.sub_off[k])
+    if ((h.sub_off[k] & 255) || h.sub_off[k] < prev || h.sub_off[k] > len || h.sub_len[k] > len - h.sub_off[k])
       return lz_fail(LZ_EFORMAT, "split container: stream archive %d out of bounds", k);
     prev = h.sub_off[k] + h.sub_len[k];
   }

@@ -1,8 +1,9 @@
 // Test driver of the CPU emulation: decode an archive through the C ABI
 // (whole file, three ranges, and four reads when it has a read index) and
 // compare every byte with the source.  With a third argument, the epoch of the
-// handle's last decode is set to that first, and five decodes follow.  Prints
-// "emu ok" and exits 0 on success.
+// handle's last decode is set to that first, and five decodes follow.  A split
+// container is opened, decoded and compared.  Prints "emu ok" and exits 0 on
+// success.
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -33,11 +34,33 @@ static bool differs(const void* a, const void* b, size_t n) { return n && std::m
 
 #define CHECK(x) do { int rc_ = (x); if (rc_) { std::fprintf(stderr, "%s -> %d: %s\n", #x, rc_, lz_last_error()); return 1; } } while (0)
 
+static int split(const uint8_t* d, uint64_t len, const std::vector<uint8_t>& src) {
+  lz_split_info info;
+  CHECK(lz_split_info_get(d, len, nullptr, &info));
+  uint8_t* ws = aligned(info.workspace_bytes);
+  lz_split* sp = nullptr;
+  CHECK(lz_split_open(d, len, ws, info.workspace_bytes, nullptr, &sp));
+  uint8_t* out = aligned(info.n);
+  CHECK(lz_split_decode_all(sp, out, info.n, nullptr));
+  CHECK(lz_split_sync_status(sp, nullptr));
+  if (info.n != src.size() || differs(out, src.data(), info.n)) { std::fprintf(stderr, "split decode differs\n"); return 1; }
+  CHECK(lz_split_close(sp));
+  std::free(out);
+  std::free(ws);
+  std::printf("emu ok: split, %llu bytes\n", (unsigned long long)info.n);
+  return 0;
+}
+
 int main(int argc, char** argv) {
   if (argc < 3) { std::fprintf(stderr, "usage: emu archive source\n"); return 2; }
   std::vector<uint8_t> av = slurp(argv[1]), src = slurp(argv[2]);
   uint8_t* arc = aligned(av.size());
   std::memcpy(arc, av.data(), av.size());
+  if (av.size() > 4 && !std::memcmp(av.data(), "LZSF", 4)) {
+    const int rc = split(arc, av.size(), src);
+    std::free(arc);
+    return rc;
+  }
   lz_info info;
   CHECK(lz_info_get(arc, av.size(), &info));
   if (info.n != src.size()) { std::fprintf(stderr, "size mismatch\n"); return 1; }

@@ -140,3 +140,26 @@ def test_completion_epochs_start_again(emu, orc, tmp_path):
     a = orc.encode(x, **CASES["deep_64"][1])
     r = _run(emu, tmp_path, a, x, "0xFFFFFFFC")
     assert r.returncode == 0 and "emu ok" in r.stdout, r.stderr[-3000:]
+
+
+@pytest.mark.parametrize("what", [None, "table", "stream"])
+def test_split_sections_that_wrap_are_refused(emu, tmp_path, what):
+    """Offsets of a split container's sections so large that their sums wrap:
+    LZ_EFORMAT, nothing is read outside the container."""
+    from gen.fastq import fastq
+    from oracle import split
+    x = bytes(fastq(n_records=4, seed=1)[0])
+    a = bytearray(split.encode(x, block_log2=8))
+    if what == "table":
+        struct.pack_into("<Q", a, 24, 2 ** 64 - 8)
+    elif what == "stream":
+        struct.pack_into("<Q", a, 64, (len(a) + 65536) & ~255)
+    h = 0xcbf29ce484222325
+    for c in a[:120]:
+        h = (h ^ c) * 0x100000001b3 % 2 ** 64
+    struct.pack_into("<Q", a, 120, h)
+    r = _run(emu, tmp_path, bytes(a), x)
+    if what is None:
+        assert r.returncode == 0 and "emu ok: split" in r.stdout, r.stderr[-3000:]
+    else:
+        assert r.returncode == 1 and "-> -2:" in r.stderr and "out of bounds" in r.stderr, r.stderr[-3000:]
